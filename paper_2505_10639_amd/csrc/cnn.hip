@@ -30,6 +30,7 @@
 #include <new>
 #include <vector>
 
+#include "conv_mfma.h"
 #include "internal.h"
 #include "momfbd.h"
 
@@ -38,15 +39,6 @@ namespace {
 
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-
-__device__ __forceinline__ uint16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7f800000u) == 0x7f800000u && (u & 0x7fffffu)) return (uint16_t)((u >> 16) | 0x40u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
 
 struct GemmArgs {
   int M, N, K;
@@ -153,6 +145,8 @@ __global__ __launch_bounds__(256) void k_epilogue(long MN, int N, int splits,
   if (out16) out16[i] = f2bf(v);
 }
 
+// PLANAR: x [B][Ci][H][W] (the network's input), else [B][H][W][Ci]
+template <bool PLANAR>
 __global__ __launch_bounds__(256) void k_im2col(int B, int H, int W, int Ci,
                                                 const uint16_t* __restrict__ x,
                                                 uint16_t* __restrict__ col) {
@@ -171,8 +165,10 @@ __global__ __launch_bounds__(256) void k_im2col(int B, int H, int W, int Ci,
   const int oy = (int)(r % Ho);
   const int b = (int)(r / Ho);
   const int y = 2 * oy + ky - 1, xx = 2 * ox + kx - 1;
-  col[idx] = (y >= 0 && y < H && xx >= 0 && xx < W) ? x[(((long)b * H + y) * W + xx) * Ci + ci]
-                                                    : (uint16_t)0;
+  col[idx] = (y >= 0 && y < H && xx >= 0 && xx < W)
+                 ? (PLANAR ? x[(((long)b * Ci + ci) * H + y) * W + xx]
+                           : x[(((long)b * H + y) * W + xx) * Ci + ci])
+                 : (uint16_t)0;
 }
 
 // dx[b][y][x][ci] = sum of the im2col entries that read x[b][y][x][ci]
@@ -233,16 +229,13 @@ __global__ __launch_bounds__(256) void k_colsum(int M, int N, const uint16_t* __
   if (tid == 0) db[n] = red[0];
 }
 
-// frames [B*J][npix] FP32 -> NHWC bfloat16 [B][npix][J]:
-// 10 (f / mean - 1) per frame; one block per frame
-// (WIDE: the rounded values as floats, for momfbd_cnn_input)
-template <bool WIDE = false>
-__global__ __launch_bounds__(256) void k_norm_frames(int J, int npix, const float* __restrict__ f,
-                                                     uint16_t* __restrict__ x,
-                                                     float* __restrict__ xw = nullptr) {
+// frames [B*J][npix] FP32 -> the network's input, one bfloat16 plane per
+// frame: 10 (f / mean - 1); one block per frame (k_netin64 does the same from
+// the spectra at 64 x 64)
+__global__ __launch_bounds__(256) void k_norm_frames(int npix, const float* __restrict__ f,
+                                                     uint16_t* __restrict__ x) {
   __shared__ float red[256];
   const int u = blockIdx.x, tid = threadIdx.x;
-  const int b = u / J, j = u % J;
   const float* fu = f + (long)u * npix;
   float s = 0.f;
   for (int i = tid; i < npix; i += 256) s += fu[i];
@@ -253,11 +246,17 @@ __global__ __launch_bounds__(256) void k_norm_frames(int J, int npix, const floa
     __syncthreads();
   }
   const float inv = (float)npix / red[0];
-  for (int i = tid; i < npix; i += 256) {
-    const uint16_t h = f2bf(10.f * (fu[i] * inv - 1.f));
-    if (WIDE) xw[((long)b * npix + i) * J + j] = bf2f(h);
-    else x[((long)b * npix + i) * J + j] = h;
-  }
+  for (int i = tid; i < npix; i += 256) x[(long)u * npix + i] = f2bf(10.f * (fu[i] * inv - 1.f));
+}
+
+// the network's input as momfbd_cnn_input returns it: [B][npix][J] floats
+__global__ __launch_bounds__(256) void k_widen_input(long n, int J, int npix,
+                                                     const uint16_t* __restrict__ x,
+                                                     float* __restrict__ out) {
+  const long i = (long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const long r = i / J, b = r / npix;
+  out[i] = bf2f(x[(b * J + i % J) * npix + r % npix]);
 }
 
 constexpr int kMaxJM = 2048;
@@ -339,13 +338,6 @@ __global__ __launch_bounds__(1024) void k_burst_loss(int B, int J, int M,
   }
 }
 
-__global__ __launch_bounds__(256) void k_scale_pred(long n, int M, const float* __restrict__ z,
-                                                    const float* __restrict__ scale,
-                                                    float* __restrict__ alpha) {
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) alpha[i] = z[i] * scale[i % M];
-}
-
 __global__ void k_sum_loss(int B, const double* __restrict__ lb, double* __restrict__ loss) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
   double s = 0.0;
@@ -413,19 +405,27 @@ namespace {
 
 size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// GEMM through the partial buffer and the epilogue; the split count keeps
-// the grid near 2048 blocks when the output is small and K large.
-hipError_t gemm(const momfbd_cnn_s* n, char* ws, int M, int N, int K, const uint16_t* A, long sam,
-                long sak, const uint16_t* B, long sbk, long sbn, const float* bias, int relu,
-                float* out32, uint16_t* out16, hipStream_t s) {
+// Chunk of the k range summed as one chain (a multiple of 32): as many splits
+// of K as keep 64 x 64 tiles of the output near 2048 blocks and their partial
+// products within part_floats.  It fixes the order of every sum of a layer,
+// whichever kernel forms it.
+int split_chunk(const momfbd_cnn_s* n, int M, int N, int K) {
   const int tm = (M + 63) / 64, tn = (N + 63) / 64;
   const int kc32 = (K + 31) / 32;
   int splits = 1;
   while (splits * 2 <= kc32 && (long)tm * tn * splits * 2 <= 2048 && splits < 256) splits *= 2;
   while ((long)splits * M * N > (long)n->part_floats && splits > 1) splits /= 2;
+  return ((kc32 + splits - 1) / splits) * 32;
+}
+
+// GEMM through the partial buffer and the epilogue.
+hipError_t gemm(const momfbd_cnn_s* n, char* ws, int M, int N, int K, const uint16_t* A, long sam,
+                long sak, const uint16_t* B, long sbk, long sbn, const float* bias, int relu,
+                float* out32, uint16_t* out16, hipStream_t s) {
+  const int tm = (M + 63) / 64, tn = (N + 63) / 64;
   if ((long)M * N > (long)n->part_floats) return hipErrorInvalidValue;
-  const int kchunk = ((kc32 + splits - 1) / splits) * 32;
-  splits = (K + kchunk - 1) / kchunk;
+  const int kchunk = split_chunk(n, M, N, K);
+  const int splits = (K + kchunk - 1) / kchunk;
   float* part = reinterpret_cast<float*>(ws + n->o_part);
   GemmArgs g{M, N, K, A, sam, sak, B, sbk, sbn, part, kchunk};
   hipLaunchKernelGGL(k_gemm_bf16, dim3(tm, tn, splits), dim3(256), 0, s, g);
@@ -435,47 +435,78 @@ hipError_t gemm(const momfbd_cnn_s* n, char* ws, int M, int N, int K, const uint
   return hipGetLastError();
 }
 
-// frames of the bursts' first channel: the apodized patches
-// W(x - m) + m = IDFT(D) / N^2 of D [B][C][J][N][N/2+1], channel 0
-hipError_t frames_from_spectra(const momfbd_cnn_s* n, int B, int C, const void* D, char* ws,
-                               hipStream_t s) {
-  return launch_frames(n->N, B * n->J, n->J, C * n->J, static_cast<const float2*>(D),
-                       reinterpret_cast<float*>(ws + n->o_frames), s);
+// the network's input from the bursts' first channel: the apodized patches
+// W(x - m) + m = IDFT(D) / N^2 of D [B][C][J][N][N/2+1], channel 0, each
+// normalised, one bfloat16 plane per frame
+hipError_t input_from_spectra(const momfbd_cnn_s* n, int B, int C, const void* D, char* ws,
+                              hipStream_t s) {
+  const float2* d = static_cast<const float2*>(D);
+  uint16_t* x0 = reinterpret_cast<uint16_t*>(ws + n->o_x0);
+  if (n->N == 64) return launch_netin64(B * n->J, n->J, C * n->J, d, x0, s);
+  float* frames = reinterpret_cast<float*>(ws + n->o_frames);
+  const hipError_t e = launch_frames(n->N, B * n->J, n->J, C * n->J, d, frames, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_norm_frames, dim3(B * n->J), dim3(256), 0, s, n->N * n->N, frames, x0);
+  return hipGetLastError();
 }
 
-hipError_t run_forward(const momfbd_cnn_s* n, const float* params, const void* D, int B, int C,
-                       char* ws, hipStream_t s) {
-  hipError_t e = frames_from_spectra(n, B, C, D, ws, s);
-  if (e != hipSuccess) return e;
-  uint16_t* x0 = reinterpret_cast<uint16_t*>(ws + n->o_x0);
-  hipLaunchKernelGGL(k_norm_frames<false>, dim3(B * n->J), dim3(256), 0, s, n->J, n->N * n->N,
-                     reinterpret_cast<const float*>(ws + n->o_frames), x0, nullptr);
-  const uint16_t* w16 = reinterpret_cast<const uint16_t*>(ws + n->o_w16);
-  const uint16_t* h = x0;
-  for (size_t l = 0; l < n->layers.size(); ++l) {
-    const Layer& L = n->layers[l];
-    const float* bias = params + L.b_off;
-    const bool last = l + 1 == n->layers.size();
-    if (L.conv) {
-      uint16_t* col = reinterpret_cast<uint16_t*>(ws + n->o_col[l]);
-      const long ncol = (long)B * L.rows * L.K;
-      hipLaunchKernelGGL(k_im2col, dim3(blocks(ncol)), dim3(256), 0, s, B, L.h, L.h, L.ci, h, col);
-      uint16_t* y = reinterpret_cast<uint16_t*>(ws + n->o_y[l]);
-      e = gemm(n, ws, (int)(B * L.rows), L.co, L.K, col, L.K, 1, w16 + L.w_off, 1, L.K, bias, 1,
-               nullptr, y, s);
-      h = y;
-    } else if (!last) {
-      uint16_t* y = reinterpret_cast<uint16_t*>(ws + n->o_y[l]);
-      e = gemm(n, ws, B, L.n_out, L.n_in, h, L.n_in, 1, w16 + L.w_off, 1, L.n_in, bias, 1, nullptr,
-               y, s);
-      h = y;
-    } else {
-      e = gemm(n, ws, B, L.n_out, L.n_in, h, L.n_in, 1, w16 + L.w_off, 1, L.n_in, bias, 0,
-               reinterpret_cast<float*>(ws + n->o_z), nullptr, s);
-    }
+hipError_t run_conv1(const momfbd_cnn_s* n, int B, const uint16_t* x, const uint16_t* w,
+                     const float* bias, uint16_t* y, hipStream_t s) {
+  const Layer& L = n->layers[0];
+  const int kchunk = split_chunk(n, (int)(B * L.rows), L.co, L.K);
+  const size_t lds = conv::conv1_lds(n->N, n->J);
+  const dim3 grid(B * (n->N / 2 / conv::net_rows(n->N)));
+  auto* kernel = n->J % 4 == 0 ? &conv::k_conv1<true> : &conv::k_conv1<false>;
+  if (lds > 65536) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  return hipSuccess;
+  hipLaunchKernelGGL(kernel, grid, dim3(256), lds, s, n->N, n->J, kchunk, x, w, bias, y);
+  return hipGetLastError();
+}
+
+template <int CI, int CO, int BM, int BN, int WM, int BK>
+hipError_t run_conv(const momfbd_cnn_s* n, const Layer& L, int B, const uint16_t* x,
+                    const uint16_t* w, const float* bias, uint16_t* y, hipStream_t s) {
+  const int M = (int)(B * L.rows);
+  hipLaunchKernelGGL((conv::k_conv<CI, CO, BM, BN, WM, BK>), dim3((M + BM - 1) / BM, CO / BN),
+                     dim3(256), 0, s, M, L.h, split_chunk(n, M, CO, L.K), x, w, bias, y);
+  return hipGetLastError();
+}
+
+hipError_t run_dense(const momfbd_cnn_s* n, const Layer& L, int B, const uint16_t* x,
+                     const uint16_t* w, const float* bias, uint16_t* out16, float* out32,
+                     const float* scale, hipStream_t s) {
+  hipLaunchKernelGGL(conv::k_dense, dim3((L.n_out + 15) / 16, (B + 15) / 16), dim3(256), 0, s, B,
+                     L.n_out, L.n_in, split_chunk(n, B, L.n_out, L.n_in), x, w, bias, out16, out32,
+                     scale, n->M);
+  return hipGetLastError();
+}
+
+// Activations of every layer, and the last layer's output z into `out32`,
+// times the mode scale where `scale` is given.
+hipError_t run_forward(const momfbd_cnn_s* n, const float* params, const void* D, int B, int C,
+                       char* ws, float* out32, const float* scale, hipStream_t s) {
+  hipError_t e = input_from_spectra(n, B, C, D, ws, s);
+  const uint16_t* w16 = reinterpret_cast<const uint16_t*>(ws + n->o_w16);
+  const uint16_t* h = reinterpret_cast<const uint16_t*>(ws + n->o_x0);
+  for (int l = 0; l < 6 && e == hipSuccess; ++l) {
+    const Layer& L = n->layers[l];
+    const uint16_t* w = w16 + L.w_off;
+    const float* bias = params + L.b_off;
+    uint16_t* y = l < 5 ? reinterpret_cast<uint16_t*>(ws + n->o_y[l]) : nullptr;
+    switch (l) {
+      case 0: e = run_conv1(n, B, h, w, bias, y, s); break;
+      case 1: e = run_conv<32, 64, 64, 64, 4, 32>(n, L, B, h, w, bias, y, s); break;
+      case 2: e = run_conv<64, 128, 32, 64, 2, 64>(n, L, B, h, w, bias, y, s); break;
+      case 3: e = run_conv<128, 128, 32, 32, 2, 64>(n, L, B, h, w, bias, y, s); break;
+      case 4: e = run_dense(n, L, B, h, w, bias, y, nullptr, nullptr, s); break;
+      default: e = run_dense(n, L, B, h, w, bias, nullptr, out32, scale, s); break;
+    }
+    h = y;
+  }
+  return e;
 }
 
 // A network and a workspace that is 256-byte aligned and at least
@@ -677,12 +708,7 @@ int momfbd_cnn_forward(momfbd_cnn net, const float* params, const void* D, int B
   if (!params || !D || !alpha || C < 1) return MOMFBD_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   char* w = static_cast<char*>(ws);
-  hipError_t e = run_forward(net, params, D, B, C, w, s);
-  if (e != hipSuccess) return MOMFBD_EDEVICE;
-  const long n = (long)B * net->J * net->M;
-  hipLaunchKernelGGL(k_scale_pred, dim3(blocks(n)), dim3(256), 0, s, n, net->M,
-                     reinterpret_cast<const float*>(w + net->o_z), net->scale, alpha);
-  return status_of(hipGetLastError());
+  return status_of(run_forward(net, params, D, B, C, w, alpha, net->scale, s));
 }
 
 int momfbd_cnn_input(momfbd_cnn net, const void* D, int B, int C, float* x, void* ws,
@@ -692,11 +718,12 @@ int momfbd_cnn_input(momfbd_cnn net, const void* D, int B, int C, float* x, void
   if (!D || !x || C < 1) return MOMFBD_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   char* w = static_cast<char*>(ws);
-  hipError_t e = frames_from_spectra(net, B, C, D, w, s);
+  const hipError_t e = input_from_spectra(net, B, C, D, w, s);
   if (e != hipSuccess) return MOMFBD_EDEVICE;
-  hipLaunchKernelGGL(k_norm_frames<true>, dim3(B * net->J), dim3(256), 0, s, net->J,
-                     net->N * net->N, reinterpret_cast<const float*>(w + net->o_frames), nullptr,
-                     x);
+  const int npix = net->N * net->N;
+  const long n = (long)B * npix * net->J;
+  hipLaunchKernelGGL(k_widen_input, dim3(blocks(n)), dim3(256), 0, s, n, net->J, npix,
+                     reinterpret_cast<const uint16_t*>(w + net->o_x0), x);
   return status_of(hipGetLastError());
 }
 
@@ -708,7 +735,7 @@ int momfbd_cnn_loss_grad(momfbd_cnn net, const float* params, const void* D, int
   if (!params || !D || !target || !loss || !grad || C < 1) return MOMFBD_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   char* w = static_cast<char*>(ws);
-  hipError_t e = run_forward(net, params, D, B, C, w, s);
+  hipError_t e = run_forward(net, params, D, B, C, w, reinterpret_cast<float*>(w + net->o_z), nullptr, s);
   if (e != hipSuccess) return MOMFBD_EDEVICE;
   const int J = net->J, M = net->M, JM = J * M;
   float* dh = reinterpret_cast<float*>(w + net->o_dh);
@@ -741,7 +768,12 @@ int momfbd_cnn_loss_grad(momfbd_cnn net, const float* params, const void* D, int
       hipLaunchKernelGGL(k_relu_back, dim3(blocks(nin)), dim3(256), 0, s, nin, dh, hin, dz2);
     } else {
       const long Mrows = (long)B * L.rows;
-      const uint16_t* col = reinterpret_cast<const uint16_t*>(w + net->o_col[l]);
+      uint16_t* col = reinterpret_cast<uint16_t*>(w + net->o_col[l]);
+      const long ncol = Mrows * L.K;
+      if (l == 0)
+        hipLaunchKernelGGL(k_im2col<true>, dim3(blocks(ncol)), dim3(256), 0, s, B, L.h, L.h, L.ci, hin, col);
+      else
+        hipLaunchKernelGGL(k_im2col<false>, dim3(blocks(ncol)), dim3(256), 0, s, B, L.h, L.h, L.ci, hin, col);
       e = gemm(net, w, L.co, L.K, (int)Mrows, dz, 1, L.co, col, L.K, 1, nullptr, 0, grad + L.w_off,
                nullptr, s);
       if (e != hipSuccess) return MOMFBD_EDEVICE;

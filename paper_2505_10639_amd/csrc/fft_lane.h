@@ -103,6 +103,24 @@ MFBD_HDI float2 twmul(float2 a) {
   }
 }
 
+// The same product with its roundings fixed: of the two products of a
+// component the one fused into the add is a.x's (FUSE_Y 1: a.y's in the
+// imaginary part; 2: a.y's in both).  twmul leaves that choice to the
+// compiler, which takes one or the other depending on the code around it.
+template <int DIR, int L, int E, int FUSE_Y>
+MFBD_HDI float2 twmul_fixed(float2 a) {
+  constexpr int e = ((E % L) + L) % L;
+  if constexpr (4 * e % L == 0) {
+    return twmul<DIR, L, E>(a);
+  } else {
+    constexpr detail::CS cs = detail::cossin_2pi(e, L);
+    constexpr float c = float(cs.c);
+    constexpr float s = float(DIR * cs.s);
+    return make_float2(FUSE_Y == 2 ? fmaf(a.y, -s, a.x * c) : fmaf(a.x, c, -(a.y * s)),
+                       FUSE_Y ? fmaf(a.y, c, a.x * s) : fmaf(a.x, s, a.y * c));
+  }
+}
+
 // The constant W_L^E itself (float2), for code that needs it as a value.
 template <int DIR, int L, int E>
 MFBD_HDI float2 twval() {

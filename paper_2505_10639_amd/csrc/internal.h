@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstddef>
+#include <cstdint>
 
 namespace mfbd {
 
@@ -358,6 +359,9 @@ hipError_t launch_synth(const Dims& d, const ChanTab& ct, const float2* O, const
                         const float* noise, const float* sigma, float* field, hipStream_t s);
 hipError_t launch_frames64(int items, int per, int stride, const float2* D, float* out,
                            hipStream_t s);
+// those frames as the warm-start network reads them (64x64; k_netin64)
+hipError_t launch_netin64(int items, int per, int stride, const float2* D, uint16_t* x,
+                          hipStream_t s);
 hipError_t launch_frames96(int items, int per, int stride, const float2* D, float* out,
                            hipStream_t s);
 hipError_t launch_frames128(int items, int per, int stride, const float2* D, float* out,

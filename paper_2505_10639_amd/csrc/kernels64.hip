@@ -13,6 +13,7 @@
 //   objimg  : object spectrum -> real image / N^2
 #include <hip/hip_runtime.h>
 
+#include "bf16.h"
 #include "internal.h"
 #include "ops64.h"
 
@@ -457,6 +458,68 @@ __global__ __launch_bounds__(64) void k_objimg64(int items, int per, int stride,
                obj + (size_t)it * N * N, nullptr, 0.f);
 }
 
+// Input of the warm-start network: frame f = IDFT(D) / N^2 of item `it` (as
+// k_objimg64), then 10 (f / mean f - 1) in bfloat16, one plane per frame:
+// x[it][N][N].  The image stays in LDS between the transform and the
+// normalisation (in two launches it crossed HBM twice in FP32).  The mean is
+// the sum of 256 strided partial sums of 16 pixels (pixel i to partial i % 256,
+// in order) and a tree over them, the order k_norm_frames uses too.  3072
+// frames take 21.7 us (52 MB read, 25 MB written); the transform and a
+// normalisation pass over NHWC took 29 + 55 us.
+__global__ __launch_bounds__(64) void k_netin64(int items, int per, int stride,
+                                                const float2* __restrict__ D,
+                                                uint16_t* __restrict__ x) {
+  __shared__ float2 T[LDS_MAIN];
+  __shared__ float2 Taux[LDS_AUX];
+  constexpr int LD = N + 1;
+  static_assert(N * LD <= 2 * LDS_MAIN, "the image fits the transform's buffer");
+  const int it = blockIdx.x;
+  if (it >= items) return;
+  const int lane = threadIdx.x;
+  const float2* A = D + ((size_t)(it / per) * stride + it % per) * kUnitF2;
+  float* Tf = reinterpret_cast<float*>(T);
+  {
+    float2 X[32];
+#pragma unroll
+    for (int m = 0; m < 32; ++m) X[m] = A[sl_index(lane, m)];
+    op3_gather(A[sl_index32(lane)], Taux, lane);
+    wave_sync();
+    op3_cols(X, Taux, T, lane);
+    wave_sync();
+    float ge[32], go[32];
+    op3_rows(T, lane, ge, go);
+    wave_sync();
+    const float inv = 1.0f / (N * N);
+#pragma unroll
+    for (int n = 0; n < 32; ++n) {
+      Tf[lane * LD + 2 * n] = ge[n] * inv;
+      Tf[lane * LD + 2 * n + 1] = go[n] * inv;
+    }
+  }
+  wave_sync();
+  // partial 64 q + lane: rows q, q + 4, ... of column `lane`
+  float s[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    s[q] = 0.f;
+#pragma unroll
+    for (int t = 0; t < 16; ++t) s[q] += Tf[(q + 4 * t) * LD + lane];
+  }
+  float r = (s[0] + s[2]) + (s[1] + s[3]);
+  for (int h = 32; h > 0; h >>= 1) r += __shfl_down(r, h);
+  const float inv = (float)(N * N) / __shfl(r, 0);
+  uint2* out = reinterpret_cast<uint2*>(x + (size_t)it * N * N);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int row = 4 * i + (lane >> 4), col = 4 * (lane & 15);
+    const float* v = Tf + row * LD + col;
+    uint16_t h[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) h[e] = f2bf(10.f * (v[e] * inv - 1.f));
+    out[i * 64 + lane] = make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
+  }
+}
+
 // Synthetic frames: i = IDFT(O_k S_u) / N^2 + sigma_p n_u for unit u = (p, c, j),
 // written to the field layout [C][J][P*N][N] that the prepare kernel reads
 // with a patch grid of one column (stride N).
@@ -545,6 +608,12 @@ hipError_t launch_objimg64(const Dims& d, const float2* O, float* obj, hipStream
 hipError_t launch_frames64(int items, int per, int stride, const float2* D, float* out,
                            hipStream_t s) {
   hipLaunchKernelGGL(k_objimg64, dim3(items), dim3(64), 0, s, items, per, stride, D, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_netin64(int items, int per, int stride, const float2* D, uint16_t* x,
+                          hipStream_t s) {
+  hipLaunchKernelGGL(k_netin64, dim3(items), dim3(64), 0, s, items, per, stride, D, x);
   return hipGetLastError();
 }
 

@@ -262,7 +262,9 @@ MFBD_HDI void op3_cols(float2 (&X)[32], const float2* Taux, float2* T, int lane)
   if (b) {
     static_for<1, 32>([&](auto I) {
       constexpr int r = decltype(I)::value;
-      X[r] = twmul<+1, 64, r>(X[r]);
+      // fixed roundings: the warm-start network rounds these images to
+      // bfloat16, so they must not depend on the kernel around this operator
+      X[r] = twmul_fixed<+1, 64, r, r == 8 ? 2 : r % 2 == 0 && r < 16>(X[r]);
     });
   }
   static_for<0, 32>([&](auto I) {

@@ -10,9 +10,9 @@
 //   conv 3x3 stride 2 pad 1, 128 -> 128, ReLU     N/8 -> N/16
 //   dense 128 (N/16)^2 -> 512, ReLU               (2048 at N = 64)
 //   dense 512 -> J*M (linear), times the per-mode scale
-// Convolutions are an explicit im2col followed by one GEMM; the backward
-// pass is two GEMMs per layer (weights: dZ^T col, data: dZ W) and a gather
-// col2im.  Weights and activations are stored in bfloat16, biases, master
+// Convolutions are implicit GEMMs (conv_mfma.h): no columns and no products
+// of a layer cross memory but its activations, their gradients and the split
+// sums of its parameter gradients.  Weights and activations are stored in bfloat16, biases, master
 // weights, gradients and Adam moments in FP32.  Every reduction runs in a
 // fixed order, so results are bitwise reproducible.
 //
@@ -24,6 +24,7 @@
 // wavefront error in units of the mean mode variance.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -37,196 +38,10 @@
 namespace mfbd {
 namespace {
 
-typedef short short4v __attribute__((ext_vector_type(4)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-struct GemmArgs {
-  int M, N, K;
-  const uint16_t* A;
-  long sam, sak;        // A(m, k) = A[m*sam + k*sak]
-  const uint16_t* B;
-  long sbk, sbn;        // B(k, n) = B[k*sbk + n*sbn]
-  float* C;             // partial products [splits][M][N]
-  int kchunk;           // k range of one split, a multiple of 32
-};
-
-// C_z = A B over the split's k range.  Block = 4 waves = a 64 x 64 tile;
-// wave (wm, wn) owns 32 x 32 = 2 x 2 MFMA tiles.  Operand layout of the
-// instruction: lane l supplies A[i = l%16][k = 4(l/16) + 0..3] and
-// B[k = 4(l/16) + 0..3][j = l%16]; it returns D[4(l/16) + e][l%16].
-__global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs g) {
-  __shared__ uint16_t As[64][40];
-  __shared__ uint16_t Bs[64][40];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int m0 = blockIdx.x * 64, n0 = blockIdx.y * 64;
-  const int kb = blockIdx.z * g.kchunk;
-  const int ke = min(g.K, kb + g.kchunk);
-  const int wm = wave >> 1, wn = wave & 1;
-  const int i16 = lane & 15, kg = lane >> 4;
-  floatx4 acc[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = kb; k0 < ke; k0 += 32) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int idx = tid + 256 * e;
-      int mm, kk;
-      if (g.sak == 1) {
-        kk = idx & 31;
-        mm = idx >> 5;
-      } else {
-        mm = idx & 63;
-        kk = idx >> 6;
-      }
-      const int m = m0 + mm, k = k0 + kk;
-      As[mm][kk] = (m < g.M && k < ke) ? g.A[(long)m * g.sam + (long)k * g.sak] : (uint16_t)0;
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int idx = tid + 256 * e;
-      int nn, kk;
-      if (g.sbn == 1) {
-        nn = idx & 63;
-        kk = idx >> 6;
-      } else {
-        kk = idx & 31;
-        nn = idx >> 5;
-      }
-      const int n = n0 + nn, k = k0 + kk;
-      Bs[nn][kk] = (n < g.N && k < ke) ? g.B[(long)k * g.sbk + (long)n * g.sbn] : (uint16_t)0;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int ks = 0; ks < 32; ks += 16) {
-      short4v a[2], b[2];
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const uint16_t* pa = &As[wm * 32 + t * 16 + i16][ks + 4 * kg];
-        const uint16_t* pb = &Bs[wn * 32 + t * 16 + i16][ks + 4 * kg];
-        a[t] = short4v{(short)pa[0], (short)pa[1], (short)pa[2], (short)pa[3]};
-        b[t] = short4v{(short)pb[0], (short)pb[1], (short)pb[2], (short)pb[3]};
-      }
-#pragma unroll
-      for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < 2; ++ni)
-          acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[mi], b[ni], acc[mi][ni], 0, 0, 0);
-    }
-    __syncthreads();
-  }
-  float* Cz = g.C + (long)blockIdx.z * g.M * g.N;
-#pragma unroll
-  for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-    for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int m = m0 + wm * 32 + mi * 16 + 4 * kg + e;
-        const int n = n0 + wn * 32 + ni * 16 + i16;
-        if (m < g.M && n < g.N) Cz[(long)m * g.N + n] = acc[mi][ni][e];
-      }
-}
-
-// out = sum_z part_z (+ bias) (ReLU), as FP32 and/or bfloat16
-__global__ __launch_bounds__(256) void k_epilogue(long MN, int N, int splits,
-                                                  const float* __restrict__ part,
-                                                  const float* __restrict__ bias, int relu,
-                                                  float* __restrict__ out32,
-                                                  uint16_t* __restrict__ out16) {
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= MN) return;
-  float v = 0.f;
-  for (int z = 0; z < splits; ++z) v += part[(long)z * MN + i];
-  if (bias) v += bias[i % N];
-  if (relu) v = fmaxf(v, 0.f);
-  if (out32) out32[i] = v;
-  if (out16) out16[i] = f2bf(v);
-}
-
-// PLANAR: x [B][Ci][H][W] (the network's input), else [B][H][W][Ci]
-template <bool PLANAR>
-__global__ __launch_bounds__(256) void k_im2col(int B, int H, int W, int Ci,
-                                                const uint16_t* __restrict__ x,
-                                                uint16_t* __restrict__ col) {
-  const int Ho = H / 2, Wo = W / 2;
-  const long n = (long)B * Ho * Wo * 9 * Ci;
-  const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= n) return;
-  const int ci = (int)(idx % Ci);
-  long r = idx / Ci;
-  const int kx = (int)(r % 3);
-  r /= 3;
-  const int ky = (int)(r % 3);
-  r /= 3;
-  const int ox = (int)(r % Wo);
-  r /= Wo;
-  const int oy = (int)(r % Ho);
-  const int b = (int)(r / Ho);
-  const int y = 2 * oy + ky - 1, xx = 2 * ox + kx - 1;
-  col[idx] = (y >= 0 && y < H && xx >= 0 && xx < W)
-                 ? (PLANAR ? x[(((long)b * Ci + ci) * H + y) * W + xx]
-                           : x[(((long)b * H + y) * W + xx) * Ci + ci])
-                 : (uint16_t)0;
-}
-
-// dx[b][y][x][ci] = sum of the im2col entries that read x[b][y][x][ci]
-__global__ __launch_bounds__(256) void k_col2im(int B, int H, int W, int Ci,
-                                                const float* __restrict__ dcol,
-                                                float* __restrict__ dx) {
-  const int Ho = H / 2, Wo = W / 2;
-  const long n = (long)B * H * W * Ci;
-  const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= n) return;
-  const int ci = (int)(idx % Ci);
-  long r = idx / Ci;
-  const int x = (int)(r % W);
-  r /= W;
-  const int y = (int)(r % H);
-  const int b = (int)(r / H);
-  float s = 0.f;
-  for (int ky = 0; ky < 3; ++ky) {
-    const int ty = y + 1 - ky;
-    if (ty < 0 || (ty & 1) || ty / 2 >= Ho) continue;
-    for (int kx = 0; kx < 3; ++kx) {
-      const int tx = x + 1 - kx;
-      if (tx < 0 || (tx & 1) || tx / 2 >= Wo) continue;
-      s += dcol[(((long)b * Ho + ty / 2) * Wo + tx / 2) * (9 * Ci) + (ky * 3 + kx) * Ci + ci];
-    }
-  }
-  dx[idx] = s;
-}
-
-// dz = bfloat16(dh * [h > 0]): the ReLU of the layer that produced h
-__global__ __launch_bounds__(256) void k_relu_back(long n, const float* __restrict__ dh,
-                                                   const uint16_t* __restrict__ h,
-                                                   uint16_t* __restrict__ dz) {
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  dz[i] = f2bf(bf2f(h[i]) > 0.f ? dh[i] : 0.f);
-}
-
 __global__ __launch_bounds__(256) void k_cast_bf16(long n, const float* __restrict__ x,
                                                    uint16_t* __restrict__ y) {
   const long i = (long)blockIdx.x * 256 + threadIdx.x;
   if (i < n) y[i] = f2bf(x[i]);
-}
-
-// db[n] = sum_m dz[m][n]; one block per column, fixed-order tree
-__global__ __launch_bounds__(256) void k_colsum(int M, int N, const uint16_t* __restrict__ dz,
-                                                float* __restrict__ db) {
-  __shared__ float red[256];
-  const int n = blockIdx.x, tid = threadIdx.x;
-  float s = 0.f;
-  for (int m = tid; m < M; m += 256) s += bf2f(dz[(long)m * N + n]);
-  red[tid] = s;
-  __syncthreads();
-  for (int h = 128; h > 0; h >>= 1) {
-    if (tid < h) red[tid] += red[tid + h];
-    __syncthreads();
-  }
-  if (tid == 0) db[n] = red[0];
 }
 
 // frames [B*J][npix] FP32 -> the network's input, one bfloat16 plane per
@@ -261,7 +76,7 @@ __global__ __launch_bounds__(256) void k_widen_input(long n, int J, int npix,
 
 constexpr int kMaxJM = 2048;
 
-// Per burst: scaled prediction alpha = z * scale, loss and dL/dz.
+// Per burst: loss and dL/dz (as the bfloat16 the backward pass reads).
 // One block per burst; thread t handles (j, m) = (t / M, t % M) for
 // t = tid, tid + 1024.
 __global__ __launch_bounds__(1024) void k_burst_loss(int B, int J, int M,
@@ -271,7 +86,7 @@ __global__ __launch_bounds__(1024) void k_burst_loss(int B, int J, int M,
                                                      const float* __restrict__ weight,
                                                      const int* __restrict__ even,
                                                      double* __restrict__ loss_b,
-                                                     float* __restrict__ dz) {
+                                                     uint16_t* __restrict__ dz) {
   __shared__ float p[kMaxJM], q[kMaxJM], d1[kMaxJM], d2[kMaxJM], g[kMaxJM];
   __shared__ float e1[64], e2[64];
   __shared__ float tm[4];
@@ -329,20 +144,13 @@ __global__ __launch_bounds__(1024) void k_burst_loss(int B, int J, int M,
       for (int jj = 0; jj < J; ++jj) s += g[jj * M + m];
       gv -= s / J;
     }
-    dz[(long)b * JM + t] = gv;
+    dz[(long)b * JM + t] = f2bf(gv);
   }
   if (tid == 0) {
     double s = 0.0;
     for (int jj = 0; jj < J; ++jj) s += (double)fminf(e1[jj], e2[jj]);
     loss_b[b] = s * (double)inv;
   }
-}
-
-__global__ void k_sum_loss(int B, const double* __restrict__ lb, double* __restrict__ loss) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  double s = 0.0;
-  for (int b = 0; b < B; ++b) s += lb[b];
-  *loss = s;
 }
 
 __global__ __launch_bounds__(256) void k_adam(long n, float* __restrict__ w,
@@ -396,8 +204,8 @@ struct momfbd_cnn_s {
   float* init_std = nullptr;  // [n_params] device
   size_t ws_bytes = 0;
   // workspace offsets (bytes)
-  size_t o_frames, o_x0, o_col[4], o_y[5], o_z, o_part, o_dz, o_dh, o_dz2, o_w16, o_lossb;
-  size_t part_floats;
+  size_t o_frames, o_x0, o_y[5], o_z, o_part, o_dz, o_dz2, o_w16, o_lossb;
+  size_t part_floats;   // enters split_chunk: bounds the partial products of a layer's splits
   int device = -1;
 };
 
@@ -416,23 +224,6 @@ int split_chunk(const momfbd_cnn_s* n, int M, int N, int K) {
   while (splits * 2 <= kc32 && (long)tm * tn * splits * 2 <= 2048 && splits < 256) splits *= 2;
   while ((long)splits * M * N > (long)n->part_floats && splits > 1) splits /= 2;
   return ((kc32 + splits - 1) / splits) * 32;
-}
-
-// GEMM through the partial buffer and the epilogue.
-hipError_t gemm(const momfbd_cnn_s* n, char* ws, int M, int N, int K, const uint16_t* A, long sam,
-                long sak, const uint16_t* B, long sbk, long sbn, const float* bias, int relu,
-                float* out32, uint16_t* out16, hipStream_t s) {
-  const int tm = (M + 63) / 64, tn = (N + 63) / 64;
-  if ((long)M * N > (long)n->part_floats) return hipErrorInvalidValue;
-  const int kchunk = split_chunk(n, M, N, K);
-  const int splits = (K + kchunk - 1) / kchunk;
-  float* part = reinterpret_cast<float*>(ws + n->o_part);
-  GemmArgs g{M, N, K, A, sam, sak, B, sbk, sbn, part, kchunk};
-  hipLaunchKernelGGL(k_gemm_bf16, dim3(tm, tn, splits), dim3(256), 0, s, g);
-  const long MN = (long)M * N;
-  hipLaunchKernelGGL(k_epilogue, dim3(blocks(MN)), dim3(256), 0, s, MN, N, splits, part, bias,
-                     relu, out32, out16);
-  return hipGetLastError();
 }
 
 // the network's input from the bursts' first channel: the apodized patches
@@ -509,6 +300,58 @@ hipError_t run_forward(const momfbd_cnn_s* n, const float* params, const void* D
   return e;
 }
 
+// The rows (pixels or bursts) of one split of a layer's parameter gradients,
+// a multiple of 32, and the splits: enough blocks of 64 x 64 sums for two on
+// every CU, but at least four stages of 32 rows in each.  The first layer's
+// blocks hold all its sums, at least 16 stages each: 512 blocks at 256 bursts
+// of 64 x 64, whose partial sums are 7 MB.
+struct WgradSplit {
+  int rows, splits;
+};
+WgradSplit wgrad_split(const Layer& L, int l, int K) {
+  const int stages = (K + 31) / 32, Mo = L.conv ? L.co : L.n_out;
+  const int tiles = (L.K + 64) / 64 * ((Mo + 63) / 64);
+  int splits = l == 0 ? (stages + 15) / 16 : std::min((stages + 3) / 4, std::max(1, 512 / tiles));
+  splits = std::max(1, std::min(splits, 512));
+  const int rows = (stages + splits - 1) / splits * 32;
+  return WgradSplit{rows, (K + rows - 1) / rows};
+}
+
+// floats of every layer's split sums at `B` bursts
+long wgrad_floats(const std::vector<Layer>& layers, int B) {
+  long n = 0;
+  for (size_t l = 0; l < layers.size(); ++l) {
+    const Layer& L = layers[l];
+    n += (long)wgrad_split(L, (int)l, (int)(B * L.rows)).splits * (L.conv ? L.co : L.n_out) * (L.K + 1);
+  }
+  return n;
+}
+
+hipError_t run_wgrad1(const momfbd_cnn_s* n, int K, const WgradSplit& sp, const uint16_t* dz,
+                      const uint16_t* x, float* part, hipStream_t s) {
+  const size_t lds = conv::wgrad1_lds(n->J);
+  const int tiles = (conv::wgrad1_cols(n->J) / 16 + 3) / 4;
+  // tiles a wave and pieces a thread holds in registers: up to 14, 28 and 64 frames
+  auto* kernel = tiles <= 2 ? &conv::k_wgrad1<2, 1> : tiles <= 4 ? &conv::k_wgrad1<4, 2>
+                                                                : &conv::k_wgrad1<10, 3>;
+  if (lds > 65536) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kernel, dim3(sp.splits), dim3(256), lds, s, n->N, n->J, K, sp.rows, dz, x, part);
+  return hipGetLastError();
+}
+
+template <int CI, int CO, int BM, int BN>
+hipError_t run_conv_dx(const momfbd_cnn_s* n, const Layer& L, int B, const uint16_t* dz,
+                       const uint16_t* w, const uint16_t* h, uint16_t* dx, hipStream_t s) {
+  const int M = (int)(B * L.rows);
+  hipLaunchKernelGGL((conv::k_conv_dx<CI, CO, BM, BN>), dim3((M + BM - 1) / BM, CI / BN, 4),
+                     dim3(256), 0, s, M, L.h / 2, split_chunk(n, M, L.K, CO), dz, w, h, dx);
+  return hipGetLastError();
+}
+
 // A network and a workspace that is 256-byte aligned and at least
 // momfbd_cnn_sizes' workspace_bytes long.
 int check_ws(const momfbd_cnn_s* n, const void* ws, size_t ws_bytes) {
@@ -582,24 +425,21 @@ int momfbd_cnn_create(int N, int J, int M, int batch_max, const float* mode_scal
   const long Bm = batch_max;
   size_t o = 0;
   n->o_frames = o;
-  o = al256(o + (size_t)Bm * J * N * N * sizeof(float));
+  if (N != 64) o = al256(o + (size_t)Bm * J * N * N * sizeof(float));
   n->o_x0 = o;
   o = al256(o + (size_t)Bm * J * N * N * sizeof(uint16_t));
-  size_t max_dh = 0;
+  size_t max_dz = (size_t)Bm * std::max(J * M, 512);   // gradients of a layer's activations
   for (int l = 0; l < 4; ++l) {
     const Layer& L = n->layers[l];
-    n->o_col[l] = o;
-    o = al256(o + (size_t)Bm * L.rows * L.K * sizeof(uint16_t));
     n->o_y[l] = o;
     o = al256(o + (size_t)Bm * L.rows * L.co * sizeof(uint16_t));
-    max_dh = std::max(max_dh, (size_t)Bm * L.rows * L.K);               // dcol
-    max_dh = std::max(max_dh, (size_t)Bm * L.h * L.h * L.ci);           // dx
+    max_dz = std::max(max_dz, (size_t)Bm * L.rows * L.co);
   }
   n->o_y[4] = o;
   o = al256(o + (size_t)Bm * 512 * sizeof(uint16_t));
   n->o_z = o;
   o = al256(o + (size_t)Bm * J * M * sizeof(float));
-  // partial products: the largest GEMM output times a few splits
+  // the largest layer's products times a few splits
   size_t part = 0;
   for (const Layer& L : n->layers) {
     part = std::max(part, (size_t)Bm * L.rows * (L.conv ? L.co : L.n_out));
@@ -607,14 +447,15 @@ int momfbd_cnn_create(int N, int J, int M, int batch_max, const float* mode_scal
     part = std::max(part, (size_t)Bm * L.rows * L.K);
   }
   n->part_floats = part;
+  // split sums of the parameter gradients, at the batch that needs most
+  long sums = 0;
+  for (int B = 1; B <= batch_max; ++B) sums = std::max(sums, wgrad_floats(n->layers, B));
   n->o_part = o;
-  o = al256(o + part * sizeof(float));
+  o = al256(o + (size_t)sums * sizeof(float));
   n->o_dz = o;
-  o = al256(o + max_dh * sizeof(uint16_t));
+  o = al256(o + max_dz * sizeof(uint16_t));
   n->o_dz2 = o;
-  o = al256(o + max_dh * sizeof(uint16_t));
-  n->o_dh = o;
-  o = al256(o + max_dh * sizeof(float));
+  o = al256(o + max_dz * sizeof(uint16_t));
   n->o_w16 = o;
   o = al256(o + (size_t)n->n_params * sizeof(uint16_t));
   n->o_lossb = o;
@@ -737,63 +578,54 @@ int momfbd_cnn_loss_grad(momfbd_cnn net, const float* params, const void* D, int
   char* w = static_cast<char*>(ws);
   hipError_t e = run_forward(net, params, D, B, C, w, reinterpret_cast<float*>(w + net->o_z), nullptr, s);
   if (e != hipSuccess) return MOMFBD_EDEVICE;
-  const int J = net->J, M = net->M, JM = J * M;
-  float* dh = reinterpret_cast<float*>(w + net->o_dh);
   uint16_t* dz = reinterpret_cast<uint16_t*>(w + net->o_dz);
-  uint16_t* dz2 = reinterpret_cast<uint16_t*>(w + net->o_dz2);
+  uint16_t* dx = reinterpret_cast<uint16_t*>(w + net->o_dz2);
   const uint16_t* w16 = reinterpret_cast<const uint16_t*>(w + net->o_w16);
+  float* part = reinterpret_cast<float*>(w + net->o_part);
   double* lb = reinterpret_cast<double*>(w + net->o_lossb);
-  hipLaunchKernelGGL(k_burst_loss, dim3(B), dim3(1024), 0, s, B, J, M,
+  hipLaunchKernelGGL(k_burst_loss, dim3(B), dim3(1024), 0, s, B, net->J, net->M,
                      reinterpret_cast<const float*>(w + net->o_z), target, net->scale,
-                     net->weight, net->even,
-                     lb, dh);
-  hipLaunchKernelGGL(k_sum_loss, dim3(1), dim3(64), 0, s, B, lb, loss);
-  hipLaunchKernelGGL(k_cast_bf16, dim3(blocks((long)B * JM)), dim3(256), 0, s, (long)B * JM, dh, dz);
-  const int nl = (int)net->layers.size();
-  for (int l = nl - 1; l >= 0; --l) {
+                     net->weight, net->even, lb, dz);
+  conv::GradSums gs{};
+  long used = 0;
+  for (int l = 5; l >= 0 && e == hipSuccess; --l) {
     const Layer& L = net->layers[l];
     // input activation of this layer (bfloat16)
-    const uint16_t* hin = l == 0 ? reinterpret_cast<const uint16_t*>(w + net->o_x0)
-                                 : reinterpret_cast<const uint16_t*>(w + net->o_y[l - 1]);
-    if (!L.conv) {
-      // dW = dz^T h_in [n_out][n_in]; db = column sums; dh = dz W [B][n_in]
-      e = gemm(net, w, L.n_out, L.n_in, B, dz, 1, L.n_out, hin, L.n_in, 1, nullptr, 0,
-               grad + L.w_off, nullptr, s);
-      if (e != hipSuccess) return MOMFBD_EDEVICE;
-      hipLaunchKernelGGL(k_colsum, dim3(L.n_out), dim3(256), 0, s, B, L.n_out, dz, grad + L.b_off);
-      e = gemm(net, w, B, L.n_in, L.n_out, dz, L.n_out, 1, w16 + L.w_off, L.n_in, 1, nullptr, 0, dh,
-               nullptr, s);
-      if (e != hipSuccess) return MOMFBD_EDEVICE;
-      const long nin = (long)B * L.n_in;
-      hipLaunchKernelGGL(k_relu_back, dim3(blocks(nin)), dim3(256), 0, s, nin, dh, hin, dz2);
-    } else {
-      const long Mrows = (long)B * L.rows;
-      uint16_t* col = reinterpret_cast<uint16_t*>(w + net->o_col[l]);
-      const long ncol = Mrows * L.K;
-      if (l == 0)
-        hipLaunchKernelGGL(k_im2col<true>, dim3(blocks(ncol)), dim3(256), 0, s, B, L.h, L.h, L.ci, hin, col);
-      else
-        hipLaunchKernelGGL(k_im2col<false>, dim3(blocks(ncol)), dim3(256), 0, s, B, L.h, L.h, L.ci, hin, col);
-      e = gemm(net, w, L.co, L.K, (int)Mrows, dz, 1, L.co, col, L.K, 1, nullptr, 0, grad + L.w_off,
-               nullptr, s);
-      if (e != hipSuccess) return MOMFBD_EDEVICE;
-      hipLaunchKernelGGL(k_colsum, dim3(L.co), dim3(256), 0, s, (int)Mrows, L.co, dz,
-                         grad + L.b_off);
-      if (l == 0) break;
-      // dcol = dz W [Mrows][K] into dh; its gather into dx reuses the
-      // partial-product buffer, free again once the epilogue has run
-      e = gemm(net, w, (int)Mrows, L.K, L.co, dz, L.co, 1, w16 + L.w_off, L.K, 1, nullptr, 0, dh,
-               nullptr, s);
-      if (e != hipSuccess) return MOMFBD_EDEVICE;
-      const long nx = (long)B * L.h * L.h * L.ci;
-      float* dx = reinterpret_cast<float*>(w + net->o_part);
-      hipLaunchKernelGGL(k_col2im, dim3(blocks(nx)), dim3(256), 0, s, B, L.h, L.h, L.ci, dh, dx);
-      hipLaunchKernelGGL(k_relu_back, dim3(blocks(nx)), dim3(256), 0, s, nx, dx, hin, dz2);
+    const uint16_t* hin = reinterpret_cast<const uint16_t*>(w + (l == 0 ? net->o_x0 : net->o_y[l - 1]));
+    const uint16_t* wl = w16 + L.w_off;
+    const int Mo = L.conv ? L.co : L.n_out, K = (int)(B * L.rows);
+    const WgradSplit ws_l = wgrad_split(L, l, K);
+    gs.l[l] = conv::GradSum{used, L.w_off, Mo, L.K, ws_l.splits, 0};
+    float* pl = part + used;
+    used += (long)ws_l.splits * Mo * (L.K + 1);
+    const dim3 grid((L.K + 64) / 64, (Mo + 63) / 64, ws_l.splits);
+    switch (l) {
+      case 0: e = run_wgrad1(net, K, ws_l, dz, hin, pl, s); break;
+      case 1: hipLaunchKernelGGL(conv::k_wgrad<32>, grid, dim3(256), 0, s, Mo, L.K, K, ws_l.rows, L.h, dz, hin, pl); break;
+      case 2: hipLaunchKernelGGL(conv::k_wgrad<64>, grid, dim3(256), 0, s, Mo, L.K, K, ws_l.rows, L.h, dz, hin, pl); break;
+      case 3: hipLaunchKernelGGL(conv::k_wgrad<128>, grid, dim3(256), 0, s, Mo, L.K, K, ws_l.rows, L.h, dz, hin, pl); break;
+      default: hipLaunchKernelGGL(conv::k_wgrad<0>, grid, dim3(256), 0, s, Mo, L.K, K, ws_l.rows, 0, dz, hin, pl); break;
     }
-    uint16_t* t = dz;
-    dz = dz2;
-    dz2 = t;
+    switch (l) {
+      case 0: break;
+      case 1: e = run_conv_dx<32, 64, 64, 32>(net, L, B, dz, wl, hin, dx, s); break;
+      case 2: e = run_conv_dx<64, 128, 64, 64>(net, L, B, dz, wl, hin, dx, s); break;
+      case 3: e = run_conv_dx<128, 128, 64, 64>(net, L, B, dz, wl, hin, dx, s); break;
+      default:
+        hipLaunchKernelGGL(conv::k_dense_dx, dim3(L.n_in / 32, (B + 31) / 32), dim3(256), 0, s, B,
+                           L.n_in, L.n_out, split_chunk(net, B, L.n_in, L.n_out), dz, wl, hin, dx);
+        break;
+    }
+    std::swap(dz, dx);
   }
+  if (e != hipSuccess) return MOMFBD_EDEVICE;
+  for (int l = 0; l < 6; ++l) {
+    gs.l[l].block0 = gs.blocks;
+    const int per = conv::grad_sum_params(gs.l[l].splits);
+    gs.blocks += (int)(((long)gs.l[l].M * (gs.l[l].N + 1) + per - 1) / per);
+  }
+  hipLaunchKernelGGL(conv::k_grad_sum, dim3(gs.blocks + 1), dim3(256), 0, s, gs, part, grad, B, lb,
+                     loss);
   return status_of(hipGetLastError());
 }
 

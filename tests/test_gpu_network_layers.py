@@ -50,3 +50,33 @@ def test_prediction(N, J, M, B):
     # sums round to neighbouring values each adds at most 2^-8
     assert np.linalg.norm(pred - ref) <= 5 * 2.0 ** -8 * np.linalg.norm(ref)
     net.close()
+
+
+@pytest.mark.parametrize("N,J,M,B", CASES)
+def test_gradients(N, J, M, B):
+    net, onet, params, scale, D = setup(N, J, M, B)
+    print(f"[layers] gradients N={N} J={J} M={M} B={B}", flush=True)
+    x = net.input(D).cpu().numpy().astype(np.float64)
+    even = cnn.even_mode_mask(M)
+    p = onet.forward(x, params, bf16=True)[0][-1].reshape(B, J, M)
+    # twice the prediction, flipped on every third frame: the choice between a
+    # frame's target and its flip is clear, and no residual is a small
+    # difference of large numbers
+    flip = np.where((np.arange(J) % 3 == 0)[None, :, None] & even[None, None, :], -1.0, 1.0)
+    target = (2.0 * p * flip * scale).astype(np.float32)
+    wt = scale.astype(np.float64) ** 2 / np.mean(scale.astype(np.float64) ** 2)
+    loss, grad = net.loss_grad(D, torch.from_numpy(target).to(D.device))
+    loss, grad = float(loss.cpu()[0]), grad.cpu().numpy()
+    l_o, g_o, _ = onet.loss_grad(x, params, target / scale, even, bf16=True, weight=wt)
+    # 2^-8 for every bfloat16 rounding point of the forward and backward pass
+    # that a layer's gradient has behind it: 12 for the first three layers, 8
+    # for the last three
+    assert abs(loss - l_o) <= 2 * 5 * 2.0 ** -8 * l_o
+    errs, o = [], 0
+    for li, (kind, a, b) in enumerate(onet.layers):
+        n = b * (9 * a if kind == "conv" else a) + b
+        errs.append(np.linalg.norm(grad[o:o + n] - g_o[o:o + n]) / np.linalg.norm(g_o[o:o + n]))
+        o += n
+    print("[layers] errors", [f"{e:.1e}" for e in errs], flush=True)
+    assert all(e <= (12 if li < 3 else 8) * 2.0 ** -8 for li, e in enumerate(errs)), errs
+    net.close()

@@ -448,8 +448,10 @@ typedef struct {
                                    wave: 4, 3 or 2 with 4 waves (fewer: more,
                                    smaller workgroups, each basis chunk
                                    serving fewer rows), 2 with 8 waves; 0 on
-                                   input is 4 or 2 (get_tuning reports the
-                                   count in use)                              */
+                                   input leaves it open: with 4 waves 4 up to
+                                   256 rows and 2 beyond (as get_tuning
+                                   reports), and few rows x modes run a kernel
+                                   that stages nothing, with the same sums  */
   int phase_col_tiles;          /* phase contraction (Eq. wavefront): 16-column
                                    tiles of (patch, frame) columns per
                                    workgroup, whose coefficients it stages in
@@ -457,10 +459,11 @@ typedef struct {
   int phase_waves;              /* and its waves: 8 x 8, 4 x 8 or 8 x 16
                                    (tiles x waves) while the staged
                                    coefficients fit 128 KB of LDS; 0, 0 on
-                                   input picks 8 x 8 where it fits, else 4 x 4
-                                   or 2 x 4 (get_tuning reports the shape in
-                                   use; set_tuning also takes the automatic
-                                   shape as reported)                         */
+                                   input leaves it open: 8 x 8 up to 128
+                                   columns where it fits (run by a kernel that
+                                   stages nothing, with the same sums), else
+                                   4 x 8 (get_tuning reports the shape;
+                                   set_tuning also takes it as reported)      */
   int object_fused;             /* 1: the forward transforms and the Wiener
                                    object and loss (Eqs. object_optimization,
                                    loss_momfbd) in one launch, a workgroup per
@@ -560,9 +563,8 @@ int momfbd_group_loss_grad(momfbd_group group, void* stream);
 int momfbd_group_lbfgs_rounds(momfbd_group group, int rounds, void* stream);
 
 /* Launch schedules of a group (the fields of momfbd_tuning that apply:
- * xcd_forward, xcd_adjoint, grad_splits, grad_row_tiles 4, 3 or 2 (0: 4, or
- * 3 and 2 where the group's largest mode count reaches 176 and 224, whose
- * accumulators would not fit four tiles); grad_waves must be 4; the phase
+ * xcd_forward, xcd_adjoint, grad_splits, grad_row_tiles 4, 3 or 2 (0: 3, or
+ * 2 where the group's largest mode count exceeds 208); grad_waves must be 4; the phase
  * fields are ignored: a group's phase blocks are 4 tiles x 8 waves; a group
  * runs the forward and object pass in two launches, object_fused is
  * ignored and reported 0).  The autotuner times momfbd_group_loss_grad over

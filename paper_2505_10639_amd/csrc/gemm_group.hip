@@ -14,13 +14,14 @@ namespace {
 
 __device__ __forceinline__ int zc_of(const Dims& d) { return d.zc > 0 ? d.zc : d.C; }
 
-// grid (4 * largest zc, phase tiles of all fields)
+// grid (4 * largest zc, phase tiles of all fields): a block takes a quarter of
+// the band
 __global__ __launch_bounds__(64 * kPhaseWaves) void k_phase_group(GroupArgs ga) {
   const int2 it = ga.item[blockIdx.y];
   const FieldDesc& F = ga.fd[it.x];
   const int zc = zc_of(F.d);
   if ((int)blockIdx.x >= 4 * zc) return;
-  contract::phase_block<kPhaseCols / 16, kPhaseWaves>(blockIdx.x, it.y, F.d.P * F.d.J, F.d.J, F.d.C, zc,
+  contract::phase_block<kPhaseCols / 16, kPhaseWaves>(blockIdx.x, it.y, F.d.bandpix() / 64, F.d.P * F.d.J, F.d.J, F.d.C, zc,
                                         F.d.M, F.Mq, F.d.bandpix(), F.ZsT, F.thetat, F.alpha,
                                         F.w.phi);
 }

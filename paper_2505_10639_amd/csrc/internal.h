@@ -28,11 +28,11 @@ struct Dims {
   // order of the forward / adjoint grids, frequency pairs per thread of the
   // object kernel, waves per row tile of the gradient contraction and the
   // number of blocks its pixel sum is split over (0: grad_splits_auto) and
-  // its row tiles per block (0: 4 with 4 waves; 3 is the other 4-wave choice;
-  // 8 waves always take 2)
+  // its row tiles per wave (0: open, see grad_row_tiles_of; 4, 3 or 2 with 4
+  // waves; 8 waves always take 2)
   int xcd_fwd = 0, xcd_adj = 1, obj_ppt = 1, grad_waves = 4, grad_splits = 0, grad_rt = 0;
   // the phase contraction's block: 16-column tiles and waves per workgroup
-  // (0, 0: the widest block whose staged coefficients fit; phase_shape_of)
+  // (0, 0: open, see phase_shape_of and launch_phase)
   int phase_ct = 0, phase_waves = 0;
   // the object pass in the forward launch (k_fwdobj64) where it applies
   // (fuse_ok, set at plan creation: 64x64 patches, at most 12 units per
@@ -290,6 +290,7 @@ struct GroupArgs {
 // blocks per row tile; grad_splits_of gives the plan's split count.
 constexpr int kMaxGradSplits = 8;
 int grad_splits_auto(const Dims& d);
+int grad_splits_staged(long blocks, int nchunk);
 int grad_splits_of(const Dims& d);
 int grad_row_tiles_of(const Dims& d);
 // The phase contraction's block in use (column tiles, waves), and whether a
@@ -301,8 +302,8 @@ size_t workspace_bytes(const Dims& d);
 Workspace carve_workspace(const Dims& d, void* base);
 
 // Launchers (return hipSuccess or the launch error); dispatch on d.N.
-// ZsT: [C][(N/2)^2][Mq/8][3] and Zs: [C][Mp][(N/2)^2/8][3], the band bases in
-// turns split into three bf16 parts (eight values per uint4; contract_mfma.h).
+// ZsT and Zs: the band bases in turns split into three bf16 parts, in operand
+// order (contract_mfma.h).
 hipError_t launch_phase(const Dims& d, const float* alpha, const uint4* ZsT, int Mq,
                         const float* thetat, float* phi, hipStream_t s);
 // `active` (nullable, [P]) restricts the unit kernels to patches with a

@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <cstdlib>
 #include <cstring>
 #include <mutex>
 #include <new>
@@ -40,10 +41,11 @@ struct momfbd_plan_s {
   int shift_y[kMaxC];      // translation applied to each channel's pupil
   int shift_x[kMaxC];
   float* Ab = nullptr;     // [C][N/2][N/2]    aperture on the band
-  // the band modes in turns, split into three bf16 parts (bf16split.h),
-  // eight values per uint4: Zs [C][Mp][(N/2)^2/8][3] (pixel index fastest,
-  // rows M..Mp-1 zero) for the gradient, ZsT [C][(N/2)^2][Mq/8][3] (mode
-  // index fastest, modes M..Mq-1 zero) for the phase
+  // the band modes in turns, split into three bf16 parts (bf16split.h), eight
+  // values per uint4, in the order the matrix operands read them
+  // (contract_mfma.h): Zs [C][(N/2)^2/32][Mp/16][3][64] (eight pixels of a
+  // mode, modes M..Mp-1 zero) for the gradient, ZsT [C][(N/2)^2/16][Mq/32][3]
+  // [64] (eight modes of a pixel, modes M..Mq-1 zero) for the phase
   uint4* Zs = nullptr;
   uint4* ZsT = nullptr;
   int Mp = 0;              // M rounded up to a multiple of 16
@@ -336,24 +338,28 @@ int momfbd_plan_create(const momfbd_desc* desc, const float* pupil, const float*
   auto zval = [&](int c, int m, size_t px) {
     return m < M ? hZ[((size_t)c * M + m) * BP + px] : 0.f;
   };
-  auto put = [](uint4* dst, const Split8& sp) {
-    dst[0] = make_uint4(sp.h[0], sp.h[1], sp.h[2], sp.h[3]);
-    dst[1] = make_uint4(sp.m[0], sp.m[1], sp.m[2], sp.m[3]);
-    dst[2] = make_uint4(sp.l[0], sp.l[1], sp.l[2], sp.l[3]);
+  // one lane's eight values of an operand run of 3 parts x 64 lanes
+  auto put = [](uint4* run, int lane, const Split8& sp) {
+    run[lane] = make_uint4(sp.h[0], sp.h[1], sp.h[2], sp.h[3]);
+    run[64 + lane] = make_uint4(sp.m[0], sp.m[1], sp.m[2], sp.m[3]);
+    run[128 + lane] = make_uint4(sp.l[0], sp.l[1], sp.l[2], sp.l[3]);
   };
+  const int mt = Mp / 16, nk = Mq / 32;
   std::vector<uint4> hZs((size_t)C * Mp * (BP / 8) * 3), hZsT((size_t)C * BP * (Mq / 8) * 3);
   for (int c = 0; c < C; ++c) {
     for (int m = 0; m < Mp; ++m)
       for (size_t p8 = 0; p8 < BP / 8; ++p8) {
         float v[8];
         for (int e = 0; e < 8; ++e) v[e] = zval(c, m, 8 * p8 + e);
-        put(&hZs[(((size_t)c * Mp + m) * (BP / 8) + p8) * 3], split8(v));
+        put(&hZs[((c * (BP / 32) + p8 / 4) * mt + m / 16) * 192], (int)(p8 % 4) * 16 + m % 16,
+            split8(v));
       }
     for (size_t px = 0; px < BP; ++px)
       for (int m8 = 0; m8 < Mq / 8; ++m8) {
         float v[8];
         for (int e = 0; e < 8; ++e) v[e] = zval(c, 8 * m8 + e, px);
-        put(&hZsT[(((size_t)c * BP + px) * (Mq / 8) + m8) * 3], split8(v));
+        put(&hZsT[((c * (BP / 16) + px / 16) * nk + m8 / 4) * 192], m8 % 4 * 16 + (int)(px % 16),
+            split8(v));
       }
   }
   if (hipGetDevice(&pl->device) != hipSuccess) { delete pl; return MOMFBD_EDEVICE; }
@@ -429,7 +435,7 @@ int momfbd_plan_set_tuning(momfbd_plan plan, const momfbd_tuning* t) {
   plan->d.obj_ppt = t->object_pairs_per_thread;
   plan->d.grad_waves = t->grad_waves;
   plan->d.grad_splits = t->grad_splits;
-  plan->d.grad_rt = t->grad_row_tiles == 3 || t->grad_row_tiles == 2 ? t->grad_row_tiles : 0;
+  plan->d.grad_rt = t->grad_waves == 8 ? 0 : t->grad_row_tiles;
   plan->d.fuse_obj = t->object_fused;
   return MOMFBD_OK;
 }
@@ -844,20 +850,20 @@ int momfbd_plan_autotune(momfbd_plan plan, const float* alpha, const void* D, co
   // far only when at least 1% faster, so that timing noise between
   // near-equal schedules does not decide (the XCD-grouped orders read less
   // from HBM at equal speed).
-  // The gradient's shape is one knob: 4 waves with 4, 3 or 2 row tiles, or
-  // 8 waves with 2 (each with its automatic split count); its split count
+  // The gradient's shape is one knob: the open schedule, 4 waves with 4, 3 or
+  // 2 row tiles, or 8 waves with 2 (each with its automatic split count); its split count
   // is the next knob, starting from the automatic one for the chosen shape,
   // the others following in increasing order.  After the last knob, one
   // whole evaluation under the chosen schedules leaves the loss and
   // gradient outputs of that schedule.  Knobs 0-5 time the adjoint, the
   // forward, the object kernel, (3, 4) the gradient contraction and (5) the
-  // phase contraction, whose candidates are its automatic block and the
-  // selectable blocks (4 x 8, 8 x 16 tiles x waves) that fit; knob 6, where
+  // phase contraction, whose candidates are its open schedule and the
+  // selectable blocks (8 x 8, 4 x 8, 8 x 16 tiles x waves) that fit; knob 6, where
   // the plan allows it, the forward and object pass in two launches (the
   // default, under the schedules chosen for them) against one.
   constexpr int kRounds = 3;
-  static const int kShapes[4][2] = {{4, 0}, {4, 3}, {4, 2}, {8, 0}};
-  static const int kPhaseShapes[3][2] = {{0, 0}, {4, 8}, {8, 16}};
+  static const int kShapes[5][2] = {{4, 0}, {4, 4}, {4, 3}, {4, 2}, {8, 0}};
+  static const int kPhaseShapes[4][2] = {{0, 0}, {8, 8}, {4, 8}, {8, 16}};
   auto set_knob = [&](int k, int v) {
     switch (k) {
       case 0: plan->d.xcd_adj = v; break;
@@ -877,9 +883,9 @@ int momfbd_plan_autotune(momfbd_plan plan, const float* alpha, const void* D, co
     }
   };
   const Dims keep_d = plan->d;
-  std::vector<int> values[7] = {{1, 0}, {0, 1}, {1, 2, 4}, {0, 1, 2, 3}, {}, {0}, {}};
+  std::vector<int> values[7] = {{1, 0}, {0, 1}, {1, 2, 4}, {0, 1, 2, 3, 4}, {}, {0}, {}};
   if (plan->d.fuse_ok) values[6] = {0, 1};
-  for (int v = 1; v < 3; ++v)
+  for (int v = 1; v < 4; ++v)
     if (phase_shape_fits(kPhaseShapes[v][0], kPhaseShapes[v][1], plan->Mq)) values[5].push_back(v);
   for (int k = 0; k < 7 && st == MOMFBD_OK; ++k) {
     if (k == 6 && values[6].empty()) break;
@@ -1025,16 +1031,15 @@ GroupArgs group_args(const momfbd_group_s* g, const FieldDesc* fd, int stage) {
   return a;
 }
 
-int group_default_rt(int mt_max) { return mt_max <= 10 ? 4 : mt_max <= 13 ? 3 : 2; }
+// 3 row tiles per wave (six uneven fields of 64 x 64, 96 x 96, 128 x 128: 665,
+// 833, 930 us an evaluation, against 689, 885, 1025 with 4 and 665, 851, 954
+// with 2), 2 where three tiles of accumulators would not fit
+int group_default_rt(int mt_max) { return mt_max <= 13 ? 3 : 2; }
 
 int group_splits(const momfbd_group_s* g) {
   if (g->grad_splits > 0) return g->grad_splits;
-  // the automatic count of a plan with all the group's rows
-  Dims d{g->N, (int)std::min<long>(g->rows, 1L << 30), 1, 1, 1, 1};
-  d.grad_waves = 4;
-  d.grad_rt = g->grad_rt == 4 ? 0 : g->grad_rt;
-  d.zc = g->zc_max;
-  return grad_splits_auto(d);
+  const long rows = 64L * g->grad_rt;
+  return grad_splits_staged((g->rows + rows - 1) / rows, g->zc_max * (g->N / 2) * (g->N / 2) / 32);
 }
 
 // One loss+gradient evaluation of every field (fd: evaluation or solver table).
@@ -1155,8 +1160,6 @@ int momfbd_group_create(const momfbd_field* fields, int n, const momfbd_lbfgs_pa
   g->zc_max = zc_max;
   g->Mq_max = Mq_max;
   g->mt_max = mt_max;
-  // default row tiles per wave: fewer for the widest mode counts, where
-  // four tiles of 16 x mt_max accumulators would spill (176 modes and up)
   g->grad_rt = group_default_rt(mt_max);
   g->rows = rows;
   const bool ok =

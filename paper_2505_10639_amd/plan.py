@@ -99,8 +99,8 @@ class Plan:
                    grad_splits=0, grad_row_tiles=0, phase_col_tiles=0, phase_waves=0,
                    object_fused=0):
         """Launch schedules (see momfbd_tuning); grad_splits 0 is automatic,
-        grad_row_tiles 0 the default for the waves, phase_col_tiles and
-        phase_waves 0 the widest phase block that fits, object_fused 1 the
+        grad_row_tiles 0 leaves the row tiles open, phase_col_tiles and
+        phase_waves 0 the phase block, object_fused 1 the
         forward and object pass in one launch where the plan allows it."""
         _lib.momfbd_plan_set_tuning(self.handle, xcd_forward, xcd_adjoint,
                                     object_pairs_per_thread, grad_waves, grad_splits,

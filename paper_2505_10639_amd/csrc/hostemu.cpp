@@ -209,6 +209,34 @@ void emu_c2r(const float* half, float* img) {
   c2r(w, X, x32, img);
 }
 
+// the same through the half-size buffer, and on through the image transposes
+// into column layout and back
+void emu_c2r_half(const float* half, float* img) {
+  static float2 X[64][32], x32[64], Xr[64][32], Taux[LDS_AUX];
+  static float Tf[LDS_HALF], ge[64][32], go[64][32], v[64][64], se[64][32], so[64][32];
+  load_sl(half, X, x32);
+  for (int l = 0; l < 64; ++l) op3_gather(x32[l], Taux, l);
+  for (int l = 0; l < 64; ++l) op3_cols_fft(X[l], Taux, l);
+  for (int l = 0; l < 64; ++l) op3_cols_put<0>(X[l], Tf, l);
+  for (int l = 0; l < 64; ++l) op3_rows_get<0>(Tf, l, Xr[l]);
+  for (int l = 0; l < 64; ++l) op3_cols_put<1>(X[l], Tf, l);
+  for (int l = 0; l < 64; ++l) op3_rows_get<1>(Tf, l, Xr[l]);
+  for (int l = 0; l < 64; ++l) op3_rows_finish(Xr[l], ge[l], go[l]);
+  for (int l = 0; l < 64; ++l) image_rows_put<0>(ge[l], go[l], Tf, l);
+  for (int l = 0; l < 64; ++l) image_cols_get<0>(Tf, l, v[l]);
+  for (int l = 0; l < 64; ++l) image_rows_put<1>(ge[l], go[l], Tf, l);
+  for (int l = 0; l < 64; ++l) image_cols_get<1>(Tf, l, v[l]);
+  for (int l = 0; l < 64; ++l)
+    for (int r = 0; r < 64; ++r) img[r * 64 + l] = v[l][r];
+  for (int l = 0; l < 64; ++l) image_cols_put<0>(v[l], Tf, l);
+  for (int l = 0; l < 64; ++l) image_rows_get<0>(Tf, l, se[l], so[l]);
+  for (int l = 0; l < 64; ++l) image_cols_put<1>(v[l], Tf, l);
+  for (int l = 0; l < 64; ++l) image_rows_get<1>(Tf, l, se[l], so[l]);
+  for (int l = 0; l < 64; ++l)
+    for (int n = 0; n < 32; ++n)
+      if (se[l][n] != ge[l][n] || so[l][n] != go[l][n]) img[0] = NAN;
+}
+
 // band pupil -> complex amplitude p [64][64] (interleaved complex)
 void emu_pupil_ifft(const float* A, const float* ph, float* p) {
   static Wave w;

@@ -209,6 +209,21 @@ __device__ __forceinline__ double object_pair(int f2, int p, int k, int C, int J
   return loss;
 }
 
+// Order of the patch cuts of `units` = P C J (patch, channel, frame) units:
+// frame by frame (f = c J + j), each frame's patches in order, and a contiguous
+// run of that order to each of the 8 XCDs (block b runs on XCD b % 8).  The
+// patches of a field overlap, so a frame is read several times: its rows then
+// come back from one L2 (patch by patch, each XCD reads every frame, and the
+// re-reads cross the fabric beside the spectra's writes).
+struct CutOrder {
+  int per;                  // blocks of an XCD
+  __host__ static CutOrder of(int units, int per_block) {
+    return CutOrder{((units + per_block - 1) / per_block + 7) / 8};
+  }
+  __host__ unsigned grid() const { return 8u * (unsigned)per; }
+  __device__ __forceinline__ int block(int b) const { return b % 8 * per + b / 8; }
+};
+
 // Smoothness prior constants per object.
 struct PriorTab {
   float gamma0[kMaxK];
@@ -356,8 +371,11 @@ hipError_t launch_objimg(const Dims& d, const float2* O, float* obj, hipStream_t
 // stride = C J)
 hipError_t launch_frames(int N, int items, int per, int stride, const float2* D, float* out,
                          hipStream_t s);
-hipError_t launch_synth(const Dims& d, const ChanTab& ct, const float2* O, const float2* S,
-                        const float* noise, const float* sigma, float* field, hipStream_t s);
+// Synthetic bursts from the phase: frames (field) and data spectra D; S is
+// scratch (not used at 64x64).
+hipError_t launch_bursts(const Dims& d, const ChanTab& ct, const float* Ab, const float* phi,
+                         float2* S, const float2* O, const float* noise, const float* sigma,
+                         const float* apod, float* field, float2* D, hipStream_t s);
 hipError_t launch_frames64(int items, int per, int stride, const float2* D, float* out,
                            hipStream_t s);
 // those frames as the warm-start network reads them (64x64; k_netin64)
@@ -381,8 +399,9 @@ hipError_t launch_adjoint64(const Dims& d, const ChanTab& ct, const LossArgs& la
 hipError_t launch_prepare64(const Dims& d, const float* frames, int H, int W, int stride,
                             const float* apod, float2* D, hipStream_t s);
 hipError_t launch_objimg64(const Dims& d, const float2* O, float* obj, hipStream_t s);
-hipError_t launch_synth64(const Dims& d, const ChanTab& ct, const float2* O, const float2* S,
-                          const float* noise, const float* sigma, float* field, hipStream_t s);
+hipError_t launch_burst64(const Dims& d, const ChanTab& ct, const float* Ab, const float* phi,
+                          const float2* O, const float* noise, const float* sigma,
+                          const float* apod, float* field, float2* D, hipStream_t s);
 hipError_t launch_forward96(const Dims& d, const ChanTab& ct, const int* active, const float* Ab,
                             const float* phi, float* psf, float2* S, hipStream_t s);
 hipError_t launch_adjoint96(const Dims& d, const ChanTab& ct, const LossArgs& la,

@@ -265,34 +265,29 @@ __global__ __launch_bounds__(kThreads) void k_adjoint128_group(GroupArgs ga, int
                   F.w.S, F.w.O, F.w.gphi);
 }
 
-__global__ __launch_bounds__(kThreads) void k_prepare128(int units, int C, int J, int H, int W,
-                                                         int stride, int nx,
+__global__ __launch_bounds__(kThreads) void k_prepare128(CutOrder order, int P, int nframes,
+                                                         int H, int W, int stride, int nx,
                                                          const float* __restrict__ frames,
                                                          const float* __restrict__ apod,
                                                          float2* __restrict__ D) {
   __shared__ float2 T[LDS_MAIN];
   __shared__ float2 Taux[LDS_AUX];
   __shared__ float red[kThreads];
-  const int u = blockIdx.x;
-  if (u >= units) return;
+  static_assert(N * 129 <= 2 * LDS_MAIN, "the image fits the transform's buffer");
+  const int unit = order.block(blockIdx.x), p = unit % P, f = unit / P;
+  if (f >= nframes) return;
   const int lane = threadIdx.x;
-  const int j = u % J;
-  const int c = (u / J) % C;
-  const int p = u / (J * C);
   const int y0 = (p / nx) * stride, x0 = (p % nx) * stride;
   float* Tf = reinterpret_cast<float*>(T);
-  const float* src = frames + ((size_t)(c * J + j) * H + y0) * W + x0;
-  for (int e = lane; e < N * N; e += kThreads) {
-    const int r = e >> 7, x = e & 127;
-    Tf[r * 129 + x] = src[(size_t)r * W + x];
-  }
-  sync();
-  const int y = lane >> 1, e = lane & 1;
+  const float* src = frames + ((size_t)f * H + y0) * W + x0;
+  // thread t holds column t % 128 of rows t / 128, + 2, ...: whole rows of the
+  // frame and of the window in every load
+  const int cx = lane & 127, cy = lane >> 7;
   float s[64];
   float sum = 0.f;
 #pragma unroll
   for (int m = 0; m < 64; ++m) {
-    s[m] = Tf[y * 129 + 2 * m + e];
+    s[m] = src[(size_t)(2 * m + cy) * W + cx];
     sum += s[m];
   }
   red[lane] = sum;
@@ -302,10 +297,16 @@ __global__ __launch_bounds__(kThreads) void k_prepare128(int units, int C, int J
     sync();
   }
   const float mean = red[0] * (1.0f / (N * N));
-  const float* wr = apod + y * N;
-  // half the apodized row (op2_rows_values takes s / 2)
+  // half the apodized image (op2_rows_values takes s / 2), through LDS into
+  // the lanes' rows
 #pragma unroll
-  for (int m = 0; m < 64; ++m) s[m] = 0.5f * (wr[2 * m + e] * (s[m] - mean) + mean);
+  for (int m = 0; m < 64; ++m)
+    Tf[(2 * m + cy) * 129 + cx] = 0.5f * (apod[(2 * m + cy) * N + cx] * (s[m] - mean) + mean);
+  sync();
+  const int y = lane >> 1, e = lane & 1;
+#pragma unroll
+  for (int m = 0; m < 64; ++m) s[m] = Tf[y * 129 + 2 * m + e];
+  sync();
   float2 X[32], x64;
   {
     float keep[32], send[32], other[32];
@@ -322,7 +323,7 @@ __global__ __launch_bounds__(kThreads) void k_prepare128(int units, int C, int J
   if (lane < 128) x64 = op2_unpack(Taux, T, lane);
   sync();
   op2_collect(T, lane, X);
-  float2* out = D + (size_t)u * kUnitF2;
+  float2* out = D + ((size_t)p * nframes + f) * kUnitF2;
 #pragma unroll
   for (int m = 0; m < 32; ++m) out[sl_index(lane, m)] = X[m];
   if (lane < 128) out[sl_index64(lane)] = x64;
@@ -360,12 +361,21 @@ __device__ __forceinline__ void inverse_item(const float2* __restrict__ A,
     xget(reinterpret_cast<const float*>(T), lane, other);
     op3_rows_finish(keep, other, lane, g);
   }
-  const int r = (lane >> 1) * N, e = lane & 1;
-  float* row = out + r;
+  // through LDS into whole rows of the image (and of the noise)
+  const int r = lane >> 1, e = lane & 1;
+  float* Tf = reinterpret_cast<float*>(T);
   const float inv = 1.0f / (N * N);
+  sync();
 #pragma unroll
-  for (int m = 0; m < 64; ++m)
-    row[2 * m + e] = g[m] * inv + (nz ? sg * nz[r + 2 * m + e] : 0.f);
+  for (int m = 0; m < 64; ++m) Tf[r * 129 + 2 * m + e] = g[m] * inv;
+  sync();
+  const int cx = lane & 127, cy = lane >> 7;
+#pragma unroll 16
+  for (int m = 0; m < 64; ++m) {
+    const int i = (2 * m + cy) * N + cx;
+    const float v = Tf[(2 * m + cy) * 129 + cx];
+    out[i] = nz ? v + sg * nz[i] : v;
+  }
 }
 
 // Item it = (it / per, it % per), `stride` items between consecutive values
@@ -439,8 +449,9 @@ hipError_t launch_prepare128(const Dims& d, const float* frames, int H, int W, i
                              const float* apod, float2* D, hipStream_t s) {
   const int units = d.P * d.C * d.J;
   const int nx = (W - N) / stride + 1;
-  hipLaunchKernelGGL(k_prepare128, dim3(units), dim3(kThreads), 0, s, units, d.C, d.J, H, W,
-                     stride, nx, frames, apod, D);
+  const CutOrder order = CutOrder::of(units, 1);
+  hipLaunchKernelGGL(k_prepare128, dim3(order.grid()), dim3(kThreads), 0, s, order, d.P, d.C * d.J, H,
+                     W, stride, nx, frames, apod, D);
   return hipGetLastError();
 }
 

@@ -11,6 +11,8 @@
 //             -> forward DFT on the pupil band -> dL/dphi = Im(conj(P) G_P)
 //   prepare : patch cut, mean removal, apodization, mean restore, 2-D DFT
 //   objimg  : object spectrum -> real image / N^2
+//   burst   : phase -> OTF -> noisy frame of an object -> data spectrum
+//   netin   : data spectrum -> the warm-start network's input
 #include <hip/hip_runtime.h>
 
 #include "bf16.h"
@@ -87,9 +89,9 @@ __device__ __forceinline__ void build_pupil(const float* __restrict__ A, const f
 // The two transposes go through a half-size buffer (real parts, then
 // imaginary parts): 9.2 KB of LDS per wave lets a CU hold the 12 waves its
 // registers allow, against 9 with the full-size buffer.
-// Unit u of a field on the wave's LDS (Th, Taux); the OTF is stored to S and
-// left in X (lane's values at sl_index) and x32 (at sl_index32).
-template <bool WANT_PSF, int SYNC>
+// Unit u of a field on the wave's LDS (Th, Taux); the OTF is stored to S
+// (STORE) and left in X (lane's values at sl_index) and x32 (at sl_index32).
+template <bool WANT_PSF, int SYNC, bool STORE = true>
 __device__ __forceinline__ void forward64_core(float2* Th, float2* Taux, int u, const ChanTab& ct,
                                                int C, int J, const int* __restrict__ active,
                                                const float* __restrict__ Ab,
@@ -149,10 +151,12 @@ __device__ __forceinline__ void forward64_core(float2* Th, float2* Taux, int u, 
   x32 = op2_unpack(Taux, Th, lane);
   unit_sync<SYNC>();
   op2_collect(Th, lane, X);
-  float2* out = S + (size_t)u * kUnitF2;
+  if constexpr (STORE) {
+    float2* out = S + (size_t)u * kUnitF2;
 #pragma unroll
-  for (int m = 0; m < 32; ++m) out[sl_index(lane, m)] = X[m];
-  out[sl_index32(lane)] = x32;
+    for (int m = 0; m < 32; ++m) out[sl_index(lane, m)] = X[m];
+    out[sl_index32(lane)] = x32;
+  }
 }
 
 // Unit u of a field (the kernel of one plan and the group kernel both
@@ -358,92 +362,115 @@ __global__ __launch_bounds__(64) void k_adjoint64_group(GroupArgs ga, int xcd) {
                  F.w.S, F.w.O, F.w.gphi);
 }
 
-__global__ __launch_bounds__(64) void k_prepare64(int units, int C, int J, int H, int W,
-                                                  int stride, int nx,
-                                                  const float* __restrict__ frames,
-                                                  const float* __restrict__ apod,
-                                                  float2* __restrict__ D) {
-  __shared__ float2 T[LDS_MAIN];
-  __shared__ float2 Taux[LDS_AUX];
-  const int u = blockIdx.x;
-  if (u >= units) return;
-  const int lane = threadIdx.x;
-  const int j = u % J;
-  const int c = (u / J) % C;
-  const int p = u / (J * C);
-  const int y0 = (p / nx) * stride, x0 = (p % nx) * stride;
-  float* Tf = reinterpret_cast<float*>(T);
-  const float* src = frames + ((size_t)(c * J + j) * H + y0) * W + x0;
-  for (int r = 0; r < N; ++r) Tf[r * 65 + lane] = src[(size_t)r * W + lane];
-  wave_sync();
-  float se[32], so[32];
-  float sum = 0.f;
+// Column layout v (lane x: all rows of column x) of a patch -> D = DFT(W (v -
+// m) + m), m its mean, stored as a half spectrum.  Whole rows of the window
+// are used in the column layout (in row layout every load instruction touched
+// 64 lines).
+template <int SYNC>
+__device__ __forceinline__ void apodized_spectrum(float (&v)[64], const float* __restrict__ apod,
+                                                  float2* Th, float2* Taux, int lane,
+                                                  float2* __restrict__ out) {
+  float* Tf = reinterpret_cast<float*>(Th);
+  float s[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int n = 0; n < 32; ++n) {
-    se[n] = Tf[lane * 65 + 2 * n];
-    so[n] = Tf[lane * 65 + 2 * n + 1];
-    sum += se[n] + so[n];
-  }
+  for (int r = 0; r < 64; ++r) s[r & 3] += v[r];
+  float sum = (s[0] + s[1]) + (s[2] + s[3]);
   for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
   const float mean = sum * (1.0f / (N * N));
-  const float* wr = apod + lane * N;
+  // half the apodized image (op2_rows_values takes s / 2)
 #pragma unroll
-  for (int n = 0; n < 32; ++n) {
-    se[n] = wr[2 * n] * (se[n] - mean) + mean;
-    so[n] = wr[2 * n + 1] * (so[n] - mean) + mean;
-  }
-  wave_sync();
-  op2_rows(se, so, T, lane);
-  wave_sync();
-  float2 X[32];
-  op2_cols(T, Taux, lane, X);
-  wave_sync();
-  const float2 x32 = op2_unpack(Taux, T, lane);
-  wave_sync();
-  op2_collect(T, lane, X);
-  float2* out = D + (size_t)u * kUnitF2;
+  for (int r = 0; r < 64; ++r) v[r] = 0.5f * (apod[r * N + lane] * (v[r] - mean) + mean);
+  float se[32], so[32];
+  image_cols_put<0>(v, Tf, lane);
+  unit_sync<SYNC>();
+  image_rows_get<0>(Tf, lane, se, so);
+  unit_sync<SYNC>();
+  image_cols_put<1>(v, Tf, lane);
+  unit_sync<SYNC>();
+  image_rows_get<1>(Tf, lane, se, so);
+  float2 w[32], X[32];
+  op2_rows_values(se, so, w);
+  unit_sync<SYNC>();
+  op2_rows_put<0>(w, Tf, lane);
+  unit_sync<SYNC>();
+  op2_cols_get<0>(Tf, lane, X);
+  unit_sync<SYNC>();
+  op2_rows_put<1>(w, Tf, lane);
+  unit_sync<SYNC>();
+  op2_cols_get<1>(Tf, lane, X);
+  op2_cols_finish(X, Taux, lane);
+  unit_sync<SYNC>();
+  const float2 x32 = op2_unpack(Taux, Th, lane);
+  unit_sync<SYNC>();
+  op2_collect(Th, lane, X);
 #pragma unroll
   for (int m = 0; m < 32; ++m) out[sl_index(lane, m)] = X[m];
   out[sl_index32(lane)] = x32;
 }
 
-// out = IDFT(A B) / N^2 + sg nz for one half spectrum A (times B when B is
-// given; plus sg times the noise image nz when nz is given): the restored
-// object image, or a synthetic frame.
-__device__ __forceinline__ void inverse_item(const float2* __restrict__ A,
-                                             const float2* __restrict__ B,
-                                             float* __restrict__ out,
-                                             const float* __restrict__ nz, float sg) {
-  __shared__ float2 T[LDS_MAIN];
-  __shared__ float2 Taux[LDS_AUX];
-  const int lane = threadIdx.x;
-  float2 X[32];
+// A workgroup of kPrepWaves units, one per wave: the window is loaded into LDS
+// once for all of them, beside the loads of the frames.  The 23 064 units of 24
+// frames of 1024 x 1024 take 138 us (490 MB to move, 94 us at the rate of a
+// large copy; 202 us with the window read row by row): the rest is LDS, whose
+// two transposes and the window keep it as busy as the arithmetic.
+constexpr int kPrepWaves = 4;
+__global__ __launch_bounds__(64 * kPrepWaves) void k_prepare64(CutOrder order, int P, int frames_n,
+                                                               int H, int W, int stride, int nx,
+                                                               const float* __restrict__ frames,
+                                                               const float* __restrict__ apod,
+                                                               float2* __restrict__ D) {
+  __shared__ float2 lds[kPrepWaves][LDS_HALF / 2 + LDS_AUX];
+  __shared__ float win[N * N];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int g = order.block(blockIdx.x) * kPrepWaves + wave, p = g % P, f = g / P;
+  const bool on = f < frames_n;
+  float v[64];
+  if (on) {
+    const int y0 = (p / nx) * stride, x0 = (p % nx) * stride;
+    const float* src = frames + ((size_t)f * H + y0) * W + x0;
 #pragma unroll
-  for (int m = 0; m < 32; ++m)
-    X[m] = B ? cmul(A[sl_index(lane, m)], B[sl_index(lane, m)]) : A[sl_index(lane, m)];
-  op3_gather(B ? cmul(A[sl_index32(lane)], B[sl_index32(lane)]) : A[sl_index32(lane)], Taux,
-             lane);
-  wave_sync();
-  op3_cols(X, Taux, T, lane);
-  wave_sync();
-  float ge[32], go[32];
-  op3_rows(T, lane, ge, go);
-  float* row = out + lane * N;
-  const float inv = 1.0f / (N * N);
-  if (nz) {
-    const float* nr = nz + lane * N;
-#pragma unroll
-    for (int n = 0; n < 32; ++n) {
-      row[2 * n] = ge[n] * inv + sg * nr[2 * n];
-      row[2 * n + 1] = go[n] * inv + sg * nr[2 * n + 1];
-    }
-  } else {
-#pragma unroll
-    for (int n = 0; n < 32; ++n) {
-      row[2 * n] = ge[n] * inv;
-      row[2 * n + 1] = go[n] * inv;
-    }
+    for (int r = 0; r < N; ++r) v[r] = src[(size_t)r * W + lane];
   }
+#pragma unroll
+  for (int i = 0; i < N * N / (64 * kPrepWaves); ++i)
+    win[threadIdx.x + 64 * kPrepWaves * i] = apod[threadIdx.x + 64 * kPrepWaves * i];
+  __syncthreads();
+  if (!on) return;
+  apodized_spectrum<1>(v, win, lds[wave], lds[wave] + LDS_HALF / 2, lane,
+                       D + ((size_t)p * frames_n + f) * kUnitF2);
+}
+
+// Spectrum in the lanes' layout (X, x32) -> its image IDFT / N^2 in column
+// layout.
+__device__ __forceinline__ void inverse_cols(float2 (&X)[32], float2 x32, float2* Th, float2* Taux,
+                                             int lane, float (&v)[64]) {
+  float* Tf = reinterpret_cast<float*>(Th);
+  op3_gather(x32, Taux, lane);
+  wave_sync();
+  op3_cols_fft(X, Taux, lane);
+  float ge[32], go[32];
+  {
+    float2 Xr[32];
+    op3_cols_put<0>(X, Tf, lane);
+    wave_sync();
+    op3_rows_get<0>(Tf, lane, Xr);
+    wave_sync();
+    op3_cols_put<1>(X, Tf, lane);
+    wave_sync();
+    op3_rows_get<1>(Tf, lane, Xr);
+    wave_sync();
+    op3_rows_finish(Xr, ge, go);
+  }
+  image_rows_put<0>(ge, go, Tf, lane);
+  wave_sync();
+  image_cols_get<0>(Tf, lane, v);
+  wave_sync();
+  image_rows_put<1>(ge, go, Tf, lane);
+  wave_sync();
+  image_cols_get<1>(Tf, lane, v);
+  wave_sync();
+#pragma unroll
+  for (int r = 0; r < 64; ++r) v[r] *= 1.0f / (N * N);
 }
 
 // Item it = (it / per, it % per) of spectra laid out with `stride` items
@@ -452,10 +479,20 @@ __device__ __forceinline__ void inverse_item(const float2* __restrict__ A,
 __global__ __launch_bounds__(64) void k_objimg64(int items, int per, int stride,
                                                  const float2* __restrict__ O,
                                                  float* __restrict__ obj) {
+  __shared__ float2 Th[LDS_HALF / 2];
+  __shared__ float2 Taux[LDS_AUX];
   const int it = blockIdx.x;
   if (it >= items) return;
-  inverse_item(O + ((size_t)(it / per) * stride + it % per) * kUnitF2, nullptr,
-               obj + (size_t)it * N * N, nullptr, 0.f);
+  const int lane = threadIdx.x;
+  const float2* A = O + ((size_t)(it / per) * stride + it % per) * kUnitF2;
+  float2 X[32];
+#pragma unroll
+  for (int m = 0; m < 32; ++m) X[m] = A[sl_index(lane, m)];
+  float v[64];
+  inverse_cols(X, A[sl_index32(lane)], Th, Taux, lane, v);
+  float* out = obj + (size_t)it * N * N + lane;
+#pragma unroll
+  for (int r = 0; r < 64; ++r) out[r * N] = v[r];
 }
 
 // Input of the warm-start network: frame f = IDFT(D) / N^2 of item `it` (as
@@ -520,30 +557,56 @@ __global__ __launch_bounds__(64) void k_netin64(int items, int per, int stride,
   }
 }
 
-// Synthetic frames: i = IDFT(O_k S_u) / N^2 + sigma_p n_u for unit u = (p, c, j),
-// written to the field layout [C][J][P*N][N] that the prepare kernel reads
-// with a patch grid of one column (stride N).
-__global__ __launch_bounds__(64) void k_synth64(int units, int P, int C, int J, int K, ChanTab ct,
+// Synthetic bursts: unit u = (p, c, j) from its phase to its data spectrum in
+// one pass: the OTF S (as k_forward64), the frame i = IDFT(O_k S) / N^2 +
+// sigma_p n, written to the field layout [C][J][P*N][N], and D = DFT(W (i - m)
+// + m) (as k_prepare64).  S and the frame stay on chip (in three launches S
+// crossed HBM twice and the frames came back once: 23 + 54 + 33 us for 3072
+// units, now 47).  Three waves per SIMD hold those units in one round, at the
+// cost of 16 bytes of scratch a lane (55 us with two).
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_burst64(int units, int P, int C, int J, int K, ChanTab ct,
+                                                const float* __restrict__ Ab,
+                                                const float* __restrict__ phi,
                                                 const float2* __restrict__ O,
-                                                const float2* __restrict__ S,
                                                 const float* __restrict__ noise,
                                                 const float* __restrict__ sigma,
-                                                float* __restrict__ field) {
+                                                const float* __restrict__ apod,
+                                                float* __restrict__ field,
+                                                float2* __restrict__ D) {
+  __shared__ float2 Th[LDS_HALF / 2];
+  __shared__ float2 Taux[LDS_AUX];
   const int u = blockIdx.x;
   if (u >= units) return;
+  const int lane = threadIdx.x;
   const int j = u % J, c = (u / J) % C, p = u / (J * C);
-  inverse_item(O + ((size_t)p * K + ct.chan_obj[c]) * kUnitF2, S + (size_t)u * kUnitF2,
-               field + ((size_t)(c * J + j) * P + p) * N * N, noise + (size_t)u * N * N,
-               sigma[p]);
+  float2 X[32], x32;
+  forward64_core<false, 0, false>(Th, Taux, u, ct, C, J, nullptr, Ab, phi, nullptr, nullptr, X,
+                                  x32);
+  wave_sync();
+  const float2* Ok = O + ((size_t)p * K + ct.chan_obj[c]) * kUnitF2;
+#pragma unroll
+  for (int m = 0; m < 32; ++m) X[m] = cmul(Ok[sl_index(lane, m)], X[m]);
+  float v[64];
+  inverse_cols(X, cmul(Ok[sl_index32(lane)], x32), Th, Taux, lane, v);
+  const float sg = sigma[p];
+  const float* nz = noise + (size_t)u * N * N + lane;
+  float* out = field + ((size_t)(c * J + j) * P + p) * N * N + lane;
+#pragma unroll
+  for (int r = 0; r < 64; ++r) {
+    v[r] += sg * nz[r * N];
+    out[r * N] = v[r];
+  }
+  apodized_spectrum<0>(v, apod, Th, Taux, lane, D + (size_t)u * kUnitF2);
 }
 
 }  // namespace
 
-hipError_t launch_synth64(const Dims& d, const ChanTab& ct, const float2* O, const float2* S,
-                          const float* noise, const float* sigma, float* field, hipStream_t s) {
+hipError_t launch_burst64(const Dims& d, const ChanTab& ct, const float* Ab, const float* phi,
+                          const float2* O, const float* noise, const float* sigma,
+                          const float* apod, float* field, float2* D, hipStream_t s) {
   const int units = d.P * d.C * d.J;
-  hipLaunchKernelGGL(k_synth64, dim3(units), dim3(64), 0, s, units, d.P, d.C, d.J, d.K, ct, O, S,
-                     noise, sigma, field);
+  hipLaunchKernelGGL(k_burst64, dim3(units), dim3(64), 0, s, units, d.P, d.C, d.J, d.K, ct, Ab,
+                     phi, O, noise, sigma, apod, field, D);
   return hipGetLastError();
 }
 
@@ -594,8 +657,9 @@ hipError_t launch_prepare64(const Dims& d, const float* frames, int H, int W, in
                             const float* apod, float2* D, hipStream_t s) {
   const int units = d.P * d.C * d.J;
   const int nx = (W - N) / stride + 1;
-  hipLaunchKernelGGL(k_prepare64, dim3(units), dim3(64), 0, s, units, d.C, d.J, H, W, stride, nx,
-                     frames, apod, D);
+  const CutOrder order = CutOrder::of(units, kPrepWaves);
+  hipLaunchKernelGGL(k_prepare64, dim3(order.grid()), dim3(64 * kPrepWaves), 0, s, order, d.P,
+                     d.C * d.J, H, W, stride, nx, frames, apod, D);
   return hipGetLastError();
 }
 

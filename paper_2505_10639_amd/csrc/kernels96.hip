@@ -220,31 +220,32 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
                   F.w.S, F.w.O, F.w.gphi);
 }
 
-__global__ __launch_bounds__(kThreads) void k_prepare96(int units, int C, int J, int H, int W,
-                                                        int stride, int nx,
+__global__ __launch_bounds__(kThreads) void k_prepare96(CutOrder order, int P, int nframes,
+                                                        int H, int W, int stride, int nx,
                                                         const float* __restrict__ frames,
                                                         const float* __restrict__ apod,
                                                         float2* __restrict__ D) {
   __shared__ float2 T[LDS_MAIN];
   __shared__ float2 Taux[LDS_AUX];
   __shared__ float red[kThreads];
-  const int u = blockIdx.x;
-  if (u >= units) return;
+  const int unit = order.block(blockIdx.x), p = unit % P, f = unit / P;
+  if (f >= nframes) return;
   const int lane = threadIdx.x;
   const bool on = lane < LANES;
-  const int j = u % J, c = (u / J) % C, p = u / (J * C);
   const int y0 = (p / nx) * stride, x0 = (p % nx) * stride;
-  const float* src = frames + ((size_t)(c * J + j) * H + y0) * W + x0;
-  float se[48], so[48];
+  const float* src = frames + ((size_t)f * H + y0) * W + x0;
+  // pixel t + 128 i of the patch, in order: whole rows of the frame and of the
+  // window in every load
+  constexpr int kPer = N * N / kThreads;
+  static_assert(kPer * kThreads == N * N && N * 97 <= 2 * LDS_MAIN, "image layout");
+  float* Tf = reinterpret_cast<float*>(T);
+  float v[kPer];
   float sum = 0.f;
-  if (on) {
-    const float* row = src + (size_t)lane * W;
 #pragma unroll
-    for (int n = 0; n < 48; ++n) {
-      se[n] = row[2 * n];
-      so[n] = row[2 * n + 1];
-      sum += se[n] + so[n];
-    }
+  for (int i = 0; i < kPer; ++i) {
+    const int k = lane + kThreads * i, y = k / N, x = k % N;
+    v[i] = src[(size_t)y * W + x];
+    sum += v[i];
   }
   red[lane] = sum;
   sync();
@@ -253,15 +254,22 @@ __global__ __launch_bounds__(kThreads) void k_prepare96(int units, int C, int J,
     sync();
   }
   const float mean = red[0] * (1.0f / (N * N));
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    const int k = lane + kThreads * i, y = k / N, x = k % N;
+    Tf[y * 97 + x] = apod[k] * (v[i] - mean) + mean;
+  }
+  sync();
+  float se[48], so[48];
   if (on) {
-    const float* wr = apod + lane * N;
 #pragma unroll
     for (int n = 0; n < 48; ++n) {
-      se[n] = wr[2 * n] * (se[n] - mean) + mean;
-      so[n] = wr[2 * n + 1] * (so[n] - mean) + mean;
+      se[n] = Tf[lane * 97 + 2 * n];
+      so[n] = Tf[lane * 97 + 2 * n + 1];
     }
-    op2_rows(se, so, T, lane);
   }
+  sync();
+  if (on) op2_rows(se, so, T, lane);
   sync();
   float2 X[48];
   if (on) op2_cols(T, Taux, lane, X);
@@ -271,7 +279,7 @@ __global__ __launch_bounds__(kThreads) void k_prepare96(int units, int C, int J,
   sync();
   if (on) {
     op2_collect(T, lane, X);
-    float2* out = D + (size_t)u * kUnitF2;
+    float2* out = D + ((size_t)p * nframes + f) * kUnitF2;
 #pragma unroll
     for (int m = 0; m < 48; ++m) out[sl_index(lane, m)] = X[m];
     out[sl_index48(lane)] = x48;
@@ -299,16 +307,25 @@ __device__ __forceinline__ void inverse_item(const float2* __restrict__ A,
   sync();
   if (on) op3_cols(X, Taux, T, lane);
   sync();
+  // through LDS into whole rows of the image (and of the noise)
+  float ge[48], go[48];
+  if (on) op3_rows(T, lane, ge, go);
+  sync();
+  float* Tf = reinterpret_cast<float*>(T);
   if (on) {
-    float ge[48], go[48];
-    op3_rows(T, lane, ge, go);
-    float* row = out + lane * N;
     const float inv = 1.0f / (N * N);
 #pragma unroll
     for (int n = 0; n < 48; ++n) {
-      row[2 * n] = ge[n] * inv + (nz ? sg * nz[lane * N + 2 * n] : 0.f);
-      row[2 * n + 1] = go[n] * inv + (nz ? sg * nz[lane * N + 2 * n + 1] : 0.f);
+      Tf[lane * 97 + 2 * n] = ge[n] * inv;
+      Tf[lane * 97 + 2 * n + 1] = go[n] * inv;
     }
+  }
+  sync();
+#pragma unroll 12
+  for (int i = 0; i < N * N / kThreads; ++i) {
+    const int k = lane + kThreads * i, y = k / N, x = k % N;
+    const float t = Tf[y * 97 + x];
+    out[k] = nz ? t + sg * nz[k] : t;
   }
 }
 
@@ -383,8 +400,9 @@ hipError_t launch_prepare96(const Dims& d, const float* frames, int H, int W, in
                             const float* apod, float2* D, hipStream_t s) {
   const int units = d.P * d.C * d.J;
   const int nx = (W - N) / stride + 1;
-  hipLaunchKernelGGL(k_prepare96, dim3(units), dim3(kThreads), 0, s, units, d.C, d.J, H, W,
-                     stride, nx, frames, apod, D);
+  const CutOrder order = CutOrder::of(units, 1);
+  hipLaunchKernelGGL(k_prepare96, dim3(order.grid()), dim3(kThreads), 0, s, order, d.P, d.C * d.J, H,
+                     W, stride, nx, frames, apod, D);
   return hipGetLastError();
 }
 

@@ -665,14 +665,10 @@ int momfbd_synthesize(momfbd_plan plan, const float* alpha, const void* O, const
   if ((st = pending_error())) return st;
   hipStream_t s = (hipStream_t)stream;
   const Workspace w = carve_workspace(plan->d, ws);
-  const int N = plan->d.N;
   hipError_t e = launch_phase(plan->d, alpha, plan->ZsT, plan->Mq, plan->thetat, w.phi, s);
-  if (e == hipSuccess) e = launch_forward(plan->d, plan->ct, nullptr, plan->Ab, w.phi, nullptr, w.S, s);
   if (e == hipSuccess)
-    e = launch_synth(plan->d, plan->ct, static_cast<const float2*>(O), w.S, noise, sigma, frames,
-                     s);
-  if (e == hipSuccess)
-    e = launch_prepare(plan->d, frames, plan->d.P * N, N, N, apod, static_cast<float2*>(D), s);
+    e = launch_bursts(plan->d, plan->ct, plan->Ab, w.phi, w.S, static_cast<const float2*>(O),
+                      noise, sigma, apod, frames, static_cast<float2*>(D), s);
   return to_status(e);
 }
 

@@ -208,11 +208,16 @@ hipError_t launch_frames(int N, int items, int per, int stride, const float2* D,
                    : launch_frames128(items, per, stride, D, out, s);
 }
 
-hipError_t launch_synth(const Dims& d, const ChanTab& ct, const float2* O, const float2* S,
-                        const float* noise, const float* sigma, float* field, hipStream_t s) {
-  return d.N == 64   ? launch_synth64(d, ct, O, S, noise, sigma, field, s)
-         : d.N == 96 ? launch_synth96(d, ct, O, S, noise, sigma, field, s)
-                     : launch_synth128(d, ct, O, S, noise, sigma, field, s);
+hipError_t launch_bursts(const Dims& d, const ChanTab& ct, const float* Ab, const float* phi,
+                         float2* S, const float2* O, const float* noise, const float* sigma,
+                         const float* apod, float* field, float2* D, hipStream_t s) {
+  if (d.N == 64)
+    return launch_burst64(d, ct, Ab, phi, O, noise, sigma, apod, field, D, s);
+  hipError_t e = launch_forward(d, ct, nullptr, Ab, phi, nullptr, S, s);
+  if (e == hipSuccess)
+    e = d.N == 96 ? launch_synth96(d, ct, O, S, noise, sigma, field, s)
+                  : launch_synth128(d, ct, O, S, noise, sigma, field, s);
+  return e != hipSuccess ? e : launch_prepare(d, field, d.P * d.N, d.N, d.N, apod, D, s);
 }
 
 hipError_t launch_objimg(const Dims& d, const float2* O, float* obj, hipStream_t s) {

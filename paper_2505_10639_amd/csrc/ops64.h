@@ -248,7 +248,7 @@ MFBD_HDI void op2_cols_finish(float2 (&X)[32], float2* Taux, int lane) {
 // ---------------------------------------------------------------------------
 MFBD_HDI void op3_gather(float2 x32, float2* Taux, int lane) { Taux[lane] = x32; }
 
-MFBD_HDI void op3_cols(float2 (&X)[32], const float2* Taux, float2* T, int lane) {
+MFBD_HDI void op3_cols_fft(float2 (&X)[32], const float2* Taux, int lane) {
   const int q = lane >> 1, b = lane & 1;
   if (q == 0) {
     // pack column 0 with column 32: both inverse transforms are real
@@ -267,22 +267,17 @@ MFBD_HDI void op3_cols(float2 (&X)[32], const float2* Taux, float2* T, int lane)
       X[r] = twmul_fixed<+1, 64, r, r == 8 ? 2 : r % 2 == 0 && r < 16>(X[r]);
     });
   }
+}
+
+MFBD_HDI void op3_cols(float2 (&X)[32], const float2* Taux, float2* T, int lane) {
+  op3_cols_fft(X, Taux, lane);
   static_for<0, 32>([&](auto I) {
     constexpr int r = decltype(I)::value;
     T[r * T3 + lane] = X[r];     // lane = 2q + b
   });
 }
 
-// Output: ge[n] = g(r, 2n), go[n] = g(r, 2n+1) for r = lane.
-MFBD_HDI void op3_rows(const float2* T, int lane, float (&ge)[32], float (&go)[32]) {
-  const int rp = lane & 31;
-  const float sg = (lane < 32) ? 1.0f : -1.0f;
-  float2 Xr[32];
-  static_for<0, 32>([&](auto Q) {
-    constexpr int q = decltype(Q)::value;
-    float2 e = T[rp * T3 + 2 * q], wo = T[rp * T3 + 2 * q + 1];
-    Xr[q] = make_float2(e.x + sg * wo.x, e.y + sg * wo.y);
-  });
+MFBD_HDI void op3_rows_finish(const float2 (&Xr)[32], float (&ge)[32], float (&go)[32]) {
   // Xr[0] = (X(r,0), X(r,32)), both real; Xr[k] = X(r,k) for k in [1,32)
   float2 Z[32];
   Z[0] = make_float2(Xr[0].x + Xr[0].y, Xr[0].x - Xr[0].y);
@@ -300,6 +295,78 @@ MFBD_HDI void op3_rows(const float2* T, int lane, float (&ge)[32], float (&go)[3
     ge[n] = Z[n].x;
     go[n] = Z[n].y;
   });
+}
+
+// Output: ge[n] = g(r, 2n), go[n] = g(r, 2n+1) for r = lane.
+MFBD_HDI void op3_rows(const float2* T, int lane, float (&ge)[32], float (&go)[32]) {
+  const int rp = lane & 31;
+  const float sg = (lane < 32) ? 1.0f : -1.0f;
+  float2 Xr[32];
+  static_for<0, 32>([&](auto Q) {
+    constexpr int q = decltype(Q)::value;
+    float2 e = T[rp * T3 + 2 * q], wo = T[rp * T3 + 2 * q + 1];
+    Xr[q] = make_float2(e.x + sg * wo.x, e.y + sg * wo.y);
+  });
+  op3_rows_finish(Xr, ge, go);
+}
+
+// Half-buffer form of op 3 (real parts, then imaginary parts, as for ops 1
+// and 2): op3_cols_fft, put<0>, get<0>, put<1>, get<1>, op3_rows_finish with a
+// barrier between each.
+template <int P>
+MFBD_HDI void op3_cols_put(const float2 (&X)[32], float* Tf, int lane) {
+  static_for<0, 32>([&](auto I) {
+    constexpr int r = decltype(I)::value;
+    Tf[r * T3 + lane] = P ? X[r].y : X[r].x;
+  });
+}
+
+template <int P>
+MFBD_HDI void op3_rows_get(const float* Tf, int lane, float2 (&Xr)[32]) {
+  const int rp = lane & 31;
+  const float sg = (lane < 32) ? 1.0f : -1.0f;
+  static_for<0, 32>([&](auto Q) {
+    constexpr int q = decltype(Q)::value;
+    const float v = Tf[rp * T3 + 2 * q] + sg * Tf[rp * T3 + 2 * q + 1];
+    if (P) Xr[q].y = v; else Xr[q].x = v;
+  });
+}
+
+// Transposes of a real image between row layout (lane r: its row, as even and
+// odd columns) and column layout (lane x: v[r], all rows of its column, whose
+// loads and stores are whole rows of memory), through the half-size buffer:
+// half h moves the rows 32 h .. 32 h + 31, which lanes 32 h .. hold.  A barrier
+// between every put and get, and between the halves.
+constexpr int TI = 66;       // floats per image row (even: a lane's pairs are 8-byte)
+static_assert(32 * TI <= LDS_HALF && 32 * T3 <= LDS_HALF, "the half-size buffer holds them");
+
+template <int H>
+MFBD_HDI void image_cols_put(const float (&v)[64], float* Tf, int lane) {
+  static_for<0, 32>([&](auto I) { Tf[decltype(I)::value * TI + lane] = v[32 * H + decltype(I)::value]; });
+}
+template <int H>
+MFBD_HDI void image_rows_get(const float* Tf, int lane, float (&se)[32], float (&so)[32]) {
+  if ((lane >> 5) == H) {
+    const float2* row = reinterpret_cast<const float2*>(Tf + (lane & 31) * TI);
+    static_for<0, 32>([&](auto I) {
+      const float2 t = row[decltype(I)::value];
+      se[decltype(I)::value] = t.x;
+      so[decltype(I)::value] = t.y;
+    });
+  }
+}
+template <int H>
+MFBD_HDI void image_rows_put(const float (&ge)[32], const float (&go)[32], float* Tf, int lane) {
+  if ((lane >> 5) == H) {
+    float2* row = reinterpret_cast<float2*>(Tf + (lane & 31) * TI);
+    static_for<0, 32>([&](auto I) {
+      row[decltype(I)::value] = make_float2(ge[decltype(I)::value], go[decltype(I)::value]);
+    });
+  }
+}
+template <int H>
+MFBD_HDI void image_cols_get(const float* Tf, int lane, float (&v)[64]) {
+  static_for<0, 32>([&](auto I) { v[32 * H + decltype(I)::value] = Tf[decltype(I)::value * TI + lane]; });
 }
 
 // ---------------------------------------------------------------------------

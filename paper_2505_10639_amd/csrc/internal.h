@@ -241,8 +241,10 @@ struct FilterSpec {
 struct FilterTab {
   FilterSpec f[kMaxK];
 };
-hipError_t launch_filter(const Dims& d, const ChanTab& ct, const FilterTab& ft, const float2* D,
-                         const float* weights, const float2* S, float2* O, float* H,
+// The filters on O in place.  h: N^2 floats per (patch, object), the clipped
+// ratio of the Loefdahl-Scharmer planes on the half spectrum
+// (launch_object_filtered); H: the filters, or null.
+hipError_t launch_filter(const Dims& d, const FilterTab& ft, const float* h, float2* O, float* H,
                          hipStream_t s);
 hipError_t launch_mosaic(const Dims& d, const float* obj, int ny, int nx, int stride, int border,
                          float* out, hipStream_t s);
@@ -350,6 +352,9 @@ hipError_t launch_loss_sum(const LossSum& ls, hipStream_t s);
 hipError_t launch_object(const Dims& d, const ChanTab& ct, const LossArgs& la, const int* active,
                          const float2* S, float2* O, double* loss_pk, double* loss,
                          hipStream_t s, bool sum_loss = true);
+hipError_t launch_object_filtered(const Dims& d, const ChanTab& ct, const LossArgs& la,
+                                  const FilterTab& ft, const float2* S, float2* O, float* h,
+                                  hipStream_t s);
 // Forward and object pass in one launch (64x64 patches, one workgroup per
 // (patch, object)): S, O and the loss partials equal those of launch_forward
 // followed by launch_object with one pair per thread, bit for bit.

@@ -610,9 +610,8 @@ int momfbd_object_estimate(momfbd_plan plan, const float* alpha, const void* D,
   if ((st = pending_error())) return st;
   hipStream_t s = (hipStream_t)stream;
   Workspace w;
-  // the per-patch loss is produced on the way; it lands in the gphi scratch
-  double* scratch_loss = reinterpret_cast<double*>(carve_workspace(plan->d, ws).gphi);
-  st = run_object(plan, alpha, D, gamma, gamma_scalar, weights, nullptr, scratch_loss, ws, s, &w);
+  // (no per-patch loss: its partials stay in the workspace)
+  st = run_object(plan, alpha, D, gamma, gamma_scalar, weights, nullptr, nullptr, ws, s, &w, false);
   if (st) return st;
   return to_status(
       prof_launch(plan, KK_OBJIMG, s, [&] { return launch_objimg(plan->d, w.O, obj, s); }));
@@ -642,15 +641,24 @@ int momfbd_object_filtered(momfbd_plan plan, const float* alpha, const void* D,
   }
   if ((st = pending_error())) return st;
   hipStream_t s = (hipStream_t)stream;
-  Workspace w;
-  double* scratch_loss = reinterpret_cast<double*>(carve_workspace(plan->d, ws).gphi);
-  st = run_object(plan, alpha, D, gamma, gamma_scalar, weights, nullptr, scratch_loss, ws, s, &w);
-  if (st) return st;
-  // the filter scales O in place; momfbd_profile_repeat refuses its kind
-  hipError_t e = prof_launch(plan, KK_FILTER, s, [&] {
-    return launch_filter(plan->d, plan->ct, ft, static_cast<const float2*>(D), weights, w.S, w.O,
-                         H, s);
+  const Workspace w = carve_workspace(plan->d, ws);
+  const LossArgs la{static_cast<const float2*>(D), gamma, gamma_scalar, weights, plan->supp};
+  hipError_t e = prof_launch(plan, KK_PHASE, s, [&] {
+    return launch_phase(plan->d, alpha, plan->ZsT, plan->Mq, plan->thetat, w.phi, s);
   });
+  if (e == hipSuccess)
+    e = prof_launch(plan, KK_FORWARD, s, [&] {
+      return launch_forward(plan->d, plan->ct, nullptr, plan->Ab, w.phi, nullptr, w.S, s);
+    });
+  // the object pass leaves the filters' clipped ratios in the output's own
+  // planes (N^2 floats each), which the inverse transform overwrites last
+  if (e == hipSuccess)
+    e = prof_launch(plan, KK_OBJECT, s, [&] {
+      return launch_object_filtered(plan->d, plan->ct, la, ft, w.S, w.O, obj, s);
+    });
+  // the filter scales O in place; momfbd_profile_repeat refuses its kind
+  if (e == hipSuccess)
+    e = prof_launch(plan, KK_FILTER, s, [&] { return launch_filter(plan->d, ft, obj, w.O, H, s); });
   if (e != hipSuccess) return to_status(e);
   return to_status(
       prof_launch(plan, KK_OBJIMG, s, [&] { return launch_objimg(plan->d, w.O, obj, s); }));

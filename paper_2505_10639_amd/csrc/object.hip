@@ -63,6 +63,81 @@ __global__ __launch_bounds__(256) void k_object(int P, int C, int J, int K, Chan
   object_block<NN, PPT>(gridDim.x - 1 - blockIdx.x, C, J, K, ct, la, active, S, O, loss_part);
 }
 
+// Frequency pair f2 of a plane whose object takes the Loefdahl-Scharmer filter:
+// the Wiener object as object_pair gives it, and the filter's clipped ratio
+// H = 1 - eta sum w |S|^2 / |sum w D conj(S)|^2 (below 0.2: 0, above 1: 1) from
+// the same sums, which here read S beyond the object's support too (the filter
+// is defined by the OTFs as they are; O is zero there).
+template <int NN>
+__device__ __forceinline__ void scharmer_pair(int f2, int p, int k, int C, int J, int K,
+                                              const ChanTab& ct, const LossArgs& la, float eta,
+                                              const float2* __restrict__ S,
+                                              float2* __restrict__ O, float* __restrict__ hk) {
+  constexpr int HC = NN / 2 + 1;
+  constexpr int kUnitF2 = NN * HC;
+  const int f = 2 * f2;
+  Acc2 a;
+  for (int i = 0; i < 2; ++i) a.nr[i] = a.ni[i] = a.q[i] = a.e[i] = 0.0;
+  const int c0 = ct.obj_first[k], c1 = ct.obj_first[k + 1];
+  for (int ci = c0; ci < c1; ++ci) {
+    const int c = ct.obj_chans[ci];
+    const size_t at = ((size_t)(p * C + c) * J) * kUnitF2 + f;
+    const float4* Dc = reinterpret_cast<const float4*>(la.D + at);
+    const float4* Sc = reinterpret_cast<const float4*>(S + at);
+    const float* wc = la.weights ? la.weights + c * J : nullptr;
+    int j = 0;
+    for (; j + 6 <= J; j += 6) {
+      float4 d[6], s[6];
+#pragma unroll
+      for (int u = 0; u < 6; ++u) {
+        d[u] = stream_load(Dc + (size_t)(j + u) * (kUnitF2 / 2));
+        s[u] = stream_load(Sc + (size_t)(j + u) * (kUnitF2 / 2));
+      }
+#pragma unroll
+      for (int u = 0; u < 6; ++u) acc_unit(a, wc ? (double)wc[j + u] : 1.0, d[u], s[u]);
+    }
+    for (; j < J; ++j)
+      acc_unit(a, wc ? (double)wc[j] : 1.0, stream_load(Dc + (size_t)j * (kUnitF2 / 2)),
+               stream_load(Sc + (size_t)j * (kUnitF2 / 2)));
+  }
+  float h[2];
+  for (int i = 0; i < 2; ++i) {
+    const double mag = a.nr[i] * a.nr[i] + a.ni[i] * a.ni[i];
+    const double v = mag > 0.0 ? 1.0 - (double)eta * a.q[i] / mag : 0.0;
+    h[i] = (float)(v < 0.2 ? 0.0 : (v > 1.0 ? 1.0 : v));
+    a.q[i] += la.gamma ? (double)la.gamma[(size_t)k * kUnitF2 + f + i] : (double)la.gamma_scalar;
+  }
+  *reinterpret_cast<float2*>(hk + f) = make_float2(h[0], h[1]);
+  const bool sup = in_support(f / HC, NN, la.supp[k * HC + f % HC]) ||
+                   in_support((f + 1) / HC, NN, la.supp[k * HC + (f + 1) % HC]);
+  if (!sup) a.nr[0] = a.ni[0] = a.nr[1] = a.ni[1] = 0.0;
+  double loss = 0.0;
+  reinterpret_cast<float4*>(O + ((size_t)p * K + k) * kUnitF2)[f2] = wiener_pair(a, f, HC, loss);
+}
+
+// The object pass of a filtered restoration (no loss): every plane's Wiener
+// object, and the clipped ratio of those with the Loefdahl-Scharmer filter into
+// their N^2 floats of `h`.  One pass over D and S serves both: 130 us
+// at 961 patches of 12 frames of 64 x 64, two objects (122 without the ratio),
+// and 41 us of k_filter, which took 131 with a pass of its own.
+template <int NN>
+__global__ __launch_bounds__(256) void k_object_filtered(int C, int J, int K, ChanTab ct,
+                                                         LossArgs la, FilterTab ft,
+                                                         const float2* __restrict__ S,
+                                                         float2* __restrict__ O,
+                                                         float* __restrict__ h) {
+  constexpr int kBlocks = object_blocks(NN, 1);
+  const int blk = gridDim.x - 1 - blockIdx.x;   // last patch first, as k_object
+  const int plane = blk / kBlocks, p = plane / K, k = plane % K;
+  const int f2 = blk % kBlocks * 256 + threadIdx.x;
+  if (f2 >= NN * (NN / 2 + 1) / 2) return;
+  if (ft.f[k].kind == kFilterScharmer)
+    scharmer_pair<NN>(f2, p, k, C, J, K, ct, la, ft.f[k].noise_power, S, O,
+                      h + (size_t)plane * NN * NN);
+  else
+    (void)object_pair<NN>(f2, p, k, C, J, K, ct, la, S, O);
+}
+
 // Every (patch, object) plane of every field of a group (one pair per thread).
 template <int NN>
 __global__ __launch_bounds__(256) void k_object_group(GroupArgs ga) {
@@ -151,6 +226,17 @@ hipError_t launch_object(const Dims& d, const ChanTab& ct, const LossArgs& la, c
     launch_object_n<128>(d, ct, la, active, S, O, loss_pk, s);
   if (!sum_loss) return hipGetLastError();
   return launch_loss_sum(loss_sum_of(d, active, loss_pk, loss), s);
+}
+
+hipError_t launch_object_filtered(const Dims& d, const ChanTab& ct, const LossArgs& la,
+                                  const FilterTab& ft, const float2* S, float2* O, float* h,
+                                  hipStream_t s) {
+  auto* kernel = d.N == 64   ? &k_object_filtered<64>
+                 : d.N == 96 ? &k_object_filtered<96>
+                             : &k_object_filtered<128>;
+  hipLaunchKernelGGL(kernel, dim3(d.P * d.K * object_blocks(d.N, 1)), dim3(256), 0, s, d.C, d.J,
+                     d.K, ct, la, ft, S, O, h);
+  return hipGetLastError();
 }
 
 hipError_t launch_object_group(int N, const GroupArgs& ga_blocks, const GroupArgs& ga_patches,

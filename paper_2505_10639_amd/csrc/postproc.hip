@@ -13,8 +13,9 @@
 //            the separable cosine taper w of Sect. "Division in patches and
 //            apodization".
 //
-// The filter works on the full N x N grid in LDS (H is symmetric under
-// u -> -u, so the half spectrum reads suffice); the island search is a
+// The object pass leaves the clipped ratio on the half spectrum
+// (object.hip).  The filter works on the full N x N grid in LDS (H is symmetric
+// under u -> -u, so the half spectrum suffices); the island search is a
 // label propagation from the origin repeated until no label changes (at
 // N = 64 on one 64-bit word per row, in one wave).
 #include <hip/hip_runtime.h>
@@ -80,10 +81,8 @@ __device__ inline unsigned long long shfl64(unsigned long long v, int lane) {
 }
 
 template <int NN>
-__global__ __launch_bounds__(256) void k_filter(int C, int J, int K, ChanTab ct, FilterTab ft,
-                                                const float2* __restrict__ D,
-                                                const float* __restrict__ weights,
-                                                const float2* __restrict__ S,
+__global__ __launch_bounds__(256) void k_filter(int K, FilterTab ft,
+                                                const float* __restrict__ h0,
                                                 float2* __restrict__ O, float* __restrict__ Hout) {
   constexpr int HC = NN / 2 + 1, UNIT = NN * HC, GRID = NN * NN;
   extern __shared__ float lds[];
@@ -104,40 +103,8 @@ __global__ __launch_bounds__(256) void k_filter(int C, int J, int K, ChanTab ct,
     }
     return;
   }
-  const int c0 = ct.obj_first[k], c1 = ct.obj_first[k + 1];
-  // the clipped H on the half spectrum (into B), the loads of four frames
-  // issued before their sums (which run in frame order)
-  auto acc = [&](double w, float2 d, float2 s, double& nr, double& ni, double& den) {
-    nr += w * ((double)d.x * s.x + (double)d.y * s.y);
-    ni += w * ((double)d.y * s.x - (double)d.x * s.y);
-    den += w * ((double)s.x * s.x + (double)s.y * s.y);
-  };
-  for (int i = tid; i < UNIT; i += 256) {
-    double nr = 0.0, ni = 0.0, den = 0.0;
-    for (int ci = c0; ci < c1; ++ci) {
-      const int c = ct.obj_chans[ci];
-      const size_t u0 = (size_t)(p * C + c) * J * UNIT + i;
-      const float* wc = weights ? weights + c * J : nullptr;
-      int j = 0;
-      for (; j + 4 <= J; j += 4) {
-        float2 d[4], s[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          d[e] = D[u0 + (size_t)(j + e) * UNIT];
-          s[e] = S[u0 + (size_t)(j + e) * UNIT];
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc(wc ? (double)wc[j + e] : 1.0, d[e], s[e], nr, ni, den);
-      }
-      for (; j < J; ++j)
-        acc(wc ? (double)wc[j] : 1.0, D[u0 + (size_t)j * UNIT], S[u0 + (size_t)j * UNIT], nr, ni,
-            den);
-    }
-    const double mag = nr * nr + ni * ni;
-    double h = mag > 0.0 ? 1.0 - (double)f.noise_power * den / mag : 0.0;
-    h = h < 0.2 ? 0.0 : (h > 1.0 ? 1.0 : h);
-    B[i] = (float)h;
-  }
+  const float* hk = h0 + ((size_t)p * K + k) * GRID;
+  for (int i = tid; i < UNIT; i += 256) B[i] = hk[i];
   __syncthreads();
   // the full grid: a frequency right of the half spectrum takes its mirror
   // -u (the conjugate pair has the same |num| and den)
@@ -267,26 +234,16 @@ __global__ __launch_bounds__(256) void k_mosaic(int N, int K, int nx, int ny, in
 
 }  // namespace
 
-hipError_t launch_filter(const Dims& d, const ChanTab& ct, const FilterTab& ft, const float2* D,
-                         const float* weights, const float2* S, float2* O, float* H,
+hipError_t launch_filter(const Dims& d, const FilterTab& ft, const float* h, float2* O, float* H,
                          hipStream_t s) {
   const size_t lds = 2 * (size_t)d.N * d.N * sizeof(float);
-  if (d.N == 64) {
-    hipLaunchKernelGGL(k_filter<64>, dim3(d.P * d.K), dim3(256), lds, s, d.C, d.J, d.K, ct, ft,
-                       D, weights, S, O, H);
-  } else if (d.N == 96) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_filter<96>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  auto* kernel = d.N == 64 ? &k_filter<64> : d.N == 96 ? &k_filter<96> : &k_filter<128>;
+  if (lds > 65536) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_filter<96>, dim3(d.P * d.K), dim3(256), lds, s, d.C, d.J, d.K, ct, ft,
-                       D, weights, S, O, H);
-  } else {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_filter<128>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_filter<128>, dim3(d.P * d.K), dim3(256), lds, s, d.C, d.J, d.K, ct, ft,
-                       D, weights, S, O, H);
   }
+  hipLaunchKernelGGL(kernel, dim3(d.P * d.K), dim3(256), lds, s, d.K, ft, h, O, H);
   return hipGetLastError();
 }
 

@@ -241,9 +241,8 @@ struct FilterSpec {
 struct FilterTab {
   FilterSpec f[kMaxK];
 };
-// The filters on O in place.  h: N^2 floats per (patch, object), the clipped
-// ratio of the Loefdahl-Scharmer planes on the half spectrum
-// (launch_object_filtered); H: the filters, or null.
+// The filters on O in place.  h [P][K][N][N/2+1]: the clipped ratios of the
+// Loefdahl-Scharmer planes (launch_object_filtered); H: the filters, or null.
 hipError_t launch_filter(const Dims& d, const FilterTab& ft, const float* h, float2* O, float* H,
                          hipStream_t s);
 hipError_t launch_mosaic(const Dims& d, const float* obj, int ny, int nx, int stride, int border,

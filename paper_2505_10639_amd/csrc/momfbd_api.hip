@@ -650,15 +650,22 @@ int momfbd_object_filtered(momfbd_plan plan, const float* alpha, const void* D,
     e = prof_launch(plan, KK_FORWARD, s, [&] {
       return launch_forward(plan->d, plan->ct, nullptr, plan->Ab, w.phi, nullptr, w.S, s);
     });
-  // the object pass leaves the filters' clipped ratios in the output's own
-  // planes (N^2 floats each), which the inverse transform overwrites last
+  // The object pass leaves the filters' clipped ratios, N (N/2 + 1) floats per
+  // object, in the gradient's unused buffer, N^2 / 4 floats per frame: from three
+  // frames per object on they fit.  With fewer, in the output's own planes (N^2
+  // floats each), which the inverse transform overwrites last.
+  const Dims& d = plan->d;
+  const size_t half = (size_t)d.N * (d.N / 2 + 1);
+  float* h = (size_t)d.C * d.J * d.bandpix() >= d.K * half ? w.gphi : obj;
   if (e == hipSuccess)
     e = prof_launch(plan, KK_OBJECT, s, [&] {
-      return launch_object_filtered(plan->d, plan->ct, la, ft, w.S, w.O, obj, s);
+      return launch_object_filtered(plan->d, plan->ct, la, ft, w.S, w.O, h, s);
     });
   // the filter scales O in place; momfbd_profile_repeat refuses its kind
   if (e == hipSuccess)
-    e = prof_launch(plan, KK_FILTER, s, [&] { return launch_filter(plan->d, ft, obj, w.O, H, s); });
+    e = prof_launch(plan, KK_FILTER, s, [&] {
+      return launch_filter(plan->d, ft, h, w.O, H, s);
+    });
   if (e != hipSuccess) return to_status(e);
   return to_status(
       prof_launch(plan, KK_OBJIMG, s, [&] { return launch_objimg(plan->d, w.O, obj, s); }));

@@ -107,7 +107,8 @@ __device__ __forceinline__ void scharmer_pair(int f2, int p, int k, int C, int J
     h[i] = (float)(v < 0.2 ? 0.0 : (v > 1.0 ? 1.0 : v));
     a.q[i] += la.gamma ? (double)la.gamma[(size_t)k * kUnitF2 + f + i] : (double)la.gamma_scalar;
   }
-  *reinterpret_cast<float2*>(hk + f) = make_float2(h[0], h[1]);
+  hk[f] = h[0];
+  hk[f + 1] = h[1];
   const bool sup = in_support(f / HC, NN, la.supp[k * HC + f % HC]) ||
                    in_support((f + 1) / HC, NN, la.supp[k * HC + (f + 1) % HC]);
   if (!sup) a.nr[0] = a.ni[0] = a.nr[1] = a.ni[1] = 0.0;
@@ -117,7 +118,7 @@ __device__ __forceinline__ void scharmer_pair(int f2, int p, int k, int C, int J
 
 // The object pass of a filtered restoration (no loss): every plane's Wiener
 // object, and the clipped ratio of those with the Loefdahl-Scharmer filter into
-// their N^2 floats of `h`.  One pass over D and S serves both: 130 us
+// their half spectrum of `h`.  One pass over D and S serves both: 130 us
 // at 961 patches of 12 frames of 64 x 64, two objects (122 without the ratio),
 // and 41 us of k_filter, which took 131 with a pass of its own.
 template <int NN>
@@ -133,7 +134,7 @@ __global__ __launch_bounds__(256) void k_object_filtered(int C, int J, int K, Ch
   if (f2 >= NN * (NN / 2 + 1) / 2) return;
   if (ft.f[k].kind == kFilterScharmer)
     scharmer_pair<NN>(f2, p, k, C, J, K, ct, la, ft.f[k].noise_power, S, O,
-                      h + (size_t)plane * NN * NN);
+                      h + (size_t)plane * NN * (NN / 2 + 1));
   else
     (void)object_pair<NN>(f2, p, k, C, J, K, ct, la, S, O);
 }

@@ -103,7 +103,7 @@ __global__ __launch_bounds__(256) void k_filter(int K, FilterTab ft,
     }
     return;
   }
-  const float* hk = h0 + ((size_t)p * K + k) * GRID;
+  const float* hk = h0 + ((size_t)p * K + k) * UNIT;
   for (int i = tid; i < UNIT; i += 256) B[i] = hk[i];
   __syncthreads();
   // the full grid: a frequency right of the half spectrum takes its mirror

@@ -1090,6 +1090,7 @@ int momfbd_group_create(const momfbd_field* fields, int n, const momfbd_lbfgs_pa
   std::vector<FieldDesc> ev(n), so(n);
   std::vector<int2> maps[kGsCount];
   std::vector<char> has_eval(n, 0);
+  std::vector<int> grad_cost(n, 0);
   int zc_max = 1, Mq_max = 32, mt_max = 1;
   long rows = 0;
   for (int f = 0; f < n; ++f) {
@@ -1145,6 +1146,8 @@ int momfbd_group_create(const momfbd_field* fields, int n, const momfbd_lbfgs_pa
       if ((long)maps[s].size() + items[s] > (1L << 28)) return MOMFBD_EUNSUPPORTED;
       for (long i = 0; i < items[s]; ++i) maps[s].push_back(make_int2(f, (int)i));
     }
+    // bases x mode tiles: the length of this field's gradient blocks
+    grad_cost[f] = (d.zc > 0 ? d.zc : d.C) * ((d.M + 15) / 16);
     zc_max = std::max(zc_max, d.zc > 0 ? d.zc : d.C);
     Mq_max = std::max(Mq_max, pl->Mq);
     mt_max = std::max(mt_max, (d.M + 15) / 16);
@@ -1162,6 +1165,11 @@ int momfbd_group_create(const momfbd_field* fields, int n, const momfbd_lbfgs_pa
   g->solver = params != nullptr;
   if (params) g->params = *params;
   g->has_eval = has_eval;
+  // the longest gradient blocks first: begun last, they would run on alone
+  for (int st : {kGsGradTiles4, kGsGradTiles3, kGsGradTiles2})
+    std::stable_sort(maps[st].begin(), maps[st].end(), [&](const int2& x, const int2& y) {
+      return grad_cost[x.x] > grad_cost[y.x];
+    });
   std::vector<int2> all;
   for (int st = 0; st < kGsCount; ++st) {
     g->item_off[st] = all.size();

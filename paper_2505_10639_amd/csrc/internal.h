@@ -433,9 +433,10 @@ hipError_t launch_lbfgs_prep(const Dims& d, const LbfgsLayout& L, void* state, f
                              hipStream_t s);
 hipError_t launch_lbfgs_publish(const Dims& d, const LbfgsLayout& L, void* state,
                                 const float* alpha, float* out, hipStream_t s);
+// next: every patch also begins its next iteration, as launch_lbfgs_prep.
 hipError_t launch_lbfgs_search(const Dims& d, const LbfgsLayout& L, void* state, float* alpha,
                                int eval, double c1, double c2, int max_evals, double ftol,
-                               hipStream_t s);
+                               bool next, hipStream_t s);
 hipError_t launch_lbfgs_finish(const Dims& d, const LbfgsLayout& L, void* state, double* loss_out,
                                int* status_out, hipStream_t s);
 
@@ -457,7 +458,7 @@ hipError_t launch_forward128_group(const GroupArgs& ga, int xcd, hipStream_t s);
 hipError_t launch_adjoint128_group(const GroupArgs& ga, int xcd, hipStream_t s);
 hipError_t launch_lbfgs_prep_group(const GroupArgs& ga, hipStream_t s);
 hipError_t launch_lbfgs_search_group(const GroupArgs& ga, double c1, double c2, int max_evals,
-                                     double ftol, hipStream_t s);
+                                     double ftol, bool next, hipStream_t s);
 hipError_t launch_lbfgs_publish_group(const GroupArgs& ga_elems, hipStream_t s);
 hipError_t launch_lbfgs_finish_group(const GroupArgs& ga_patches, hipStream_t s);
 

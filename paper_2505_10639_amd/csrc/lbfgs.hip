@@ -459,19 +459,32 @@ __device__ __forceinline__ void search_patch(int p, const LbfgsLayout& L, void* 
   }
 }
 
+// One patch per block.  NEXT (a round that another follows): the patch's next
+// iteration begins here too, which saves the launch and gap of k_lbfgs_prep:
+// four rounds of 225 patches of 64 x 64 x 12 frames take 570 us, 579 before.
+template <bool NEXT>
 __global__ __launch_bounds__(kThreads) void k_lbfgs_search(LbfgsLayout L, void* state,
                                                            float* __restrict__ alpha, int eval,
                                                            double c1, double c2, int max_evals,
                                                            double ftol) {
   search_patch(blockIdx.x, L, state, alpha, eval, c1, c2, max_evals, ftol);
+  if (NEXT) {
+    __syncthreads();   // the header, gradient and history that the search wrote
+    prep_patch(blockIdx.x, L, state, alpha);
+  }
 }
 
+template <bool NEXT>
 __global__ __launch_bounds__(kThreads) void k_lbfgs_search_group(GroupArgs ga, double c1,
                                                                  double c2, int max_evals,
                                                                  double ftol) {
   const int2 it = ga.item[blockIdx.x];
   const FieldDesc& F = ga.fd[it.x];
   search_patch(it.y, F.L, F.state, F.alpha, -1, c1, c2, max_evals, ftol);
+  if (NEXT) {
+    __syncthreads();
+    prep_patch(it.y, F.L, F.state, F.alpha);
+  }
 }
 
 // The accepted point of every patch: x0 while inside a line search.
@@ -571,9 +584,10 @@ hipError_t launch_lbfgs_publish(const Dims& d, const LbfgsLayout& L, void* state
 
 hipError_t launch_lbfgs_search(const Dims& d, const LbfgsLayout& L, void* state, float* alpha,
                                int eval, double c1, double c2, int max_evals, double ftol,
-                               hipStream_t s) {
-  hipLaunchKernelGGL(k_lbfgs_search, dim3(d.P), dim3(kThreads), 0, s, L, state, alpha, eval, c1,
-                     c2, max_evals, ftol);
+                               bool next, hipStream_t s) {
+  auto* kernel = next ? &k_lbfgs_search<true> : &k_lbfgs_search<false>;
+  hipLaunchKernelGGL(kernel, dim3(d.P), dim3(kThreads), 0, s, L, state, alpha, eval, c1, c2,
+                     max_evals, ftol);
   return hipGetLastError();
 }
 
@@ -583,9 +597,9 @@ hipError_t launch_lbfgs_prep_group(const GroupArgs& ga, hipStream_t s) {
 }
 
 hipError_t launch_lbfgs_search_group(const GroupArgs& ga, double c1, double c2, int max_evals,
-                                     double ftol, hipStream_t s) {
-  hipLaunchKernelGGL(k_lbfgs_search_group, dim3(ga.total), dim3(kThreads), 0, s, ga, c1, c2,
-                     max_evals, ftol);
+                                     double ftol, bool next, hipStream_t s) {
+  auto* kernel = next ? &k_lbfgs_search_group<true> : &k_lbfgs_search_group<false>;
+  hipLaunchKernelGGL(kernel, dim3(ga.total), dim3(kThreads), 0, s, ga, c1, c2, max_evals, ftol);
   return hipGetLastError();
 }
 

@@ -756,7 +756,7 @@ int momfbd_lbfgs_step(momfbd_plan plan, const momfbd_lbfgs_params* params, void*
                        s);
     if (st) return st;
     e = launch_lbfgs_search(plan->d, L, state, alpha, ev, params->c1, params->c2,
-                            params->max_evals, params->ftol, s);
+                            params->max_evals, params->ftol, false, s);
     if (e != hipSuccess) break;
     // how many patches still search: decides whether another evaluation is needed
     e = hipMemcpyAsync(plan->hflag, counter + ev, sizeof(int), hipMemcpyDeviceToHost, s);
@@ -781,16 +781,14 @@ int momfbd_lbfgs_rounds(momfbd_plan plan, const momfbd_lbfgs_params* params, voi
   hipStream_t s = (hipStream_t)stream;
   char* b = static_cast<char*>(state);
   const int* active = reinterpret_cast<const int*>(b + L.active);
-  hipError_t e = hipSuccess;
+  hipError_t e = rounds > 0 ? launch_lbfgs_prep(plan->d, L, state, alpha, s) : hipSuccess;
   for (int r = 0; e == hipSuccess && r < rounds; ++r) {
-    e = launch_lbfgs_prep(plan->d, L, state, alpha, s);
-    if (e != hipSuccess) break;
     st = run_loss_grad(plan, alpha, D, gamma, gamma_scalar, weights, active,
                        reinterpret_cast<double*>(b + L.ft), reinterpret_cast<float*>(b + L.gt), ws,
                        s);
     if (st) return st;
     e = launch_lbfgs_search(plan->d, L, state, alpha, -1, params->c1, params->c2,
-                            params->max_evals, params->ftol, s);
+                            params->max_evals, params->ftol, r + 1 < rounds, s);
   }
   if (e == hipSuccess && alpha_accepted)
     e = launch_lbfgs_publish(plan->d, L, state, alpha, alpha_accepted, s);
@@ -1218,13 +1216,13 @@ int momfbd_group_lbfgs_rounds(momfbd_group g, int rounds, void* stream) {
   if (int st = pending_error()) return st;
   hipStream_t s = (hipStream_t)stream;
   const FieldDesc* fd = g->fd_solve;
-  hipError_t e = hipSuccess;
+  hipError_t e =
+      rounds > 0 ? launch_lbfgs_prep_group(group_args(g, fd, kGsPatches), s) : hipSuccess;
   for (int r = 0; e == hipSuccess && r < rounds; ++r) {
-    e = launch_lbfgs_prep_group(group_args(g, fd, kGsPatches), s);
-    if (e == hipSuccess) e = group_chain(g, fd, s);
+    e = group_chain(g, fd, s);
     if (e == hipSuccess)
       e = launch_lbfgs_search_group(group_args(g, fd, kGsPatches), g->params.c1, g->params.c2,
-                                    g->params.max_evals, g->params.ftol, s);
+                                    g->params.max_evals, g->params.ftol, r + 1 < rounds, s);
   }
   if (e == hipSuccess) e = launch_lbfgs_publish_group(group_args(g, fd, kGsElemBlocks), s);
   if (e == hipSuccess) e = launch_lbfgs_finish_group(group_args(g, fd, kGsPatchBlocks), s);

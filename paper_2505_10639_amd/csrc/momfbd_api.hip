@@ -294,10 +294,16 @@ int momfbd_plan_create(const momfbd_desc* desc, const float* pupil, const float*
         hA[(size_t)c * BP + dst] = A[src];
         const double th = diversity ? diversity[(size_t)c * N * N + src] : 0.0;
         hT[(size_t)c * BP + dst] = (float)(th / kTwoPi);
-        for (int m = 0; m < M; ++m)
-          hZ[((size_t)c * M + m) * BP + dst] =
-              (float)((double)basis[((size_t)c * M + m) * N * N + src] / kTwoPi);
       }
+    for (int m = 0; m < M; ++m) {
+      const float* Z = basis + ((size_t)c * M + m) * N * N;
+      float* z = hZ.data() + ((size_t)c * M + m) * BP;
+      for (int n = 0; n < B; ++n)
+        for (int qx = 0; qx < B; ++qx) {
+          const int y = ((y0 - oy + n) % N + N) % N, x = ((x0 - ox + qx) % N + N) % N;
+          z[(size_t)n * B + qx] = (float)((double)Z[(size_t)y * N + x] / kTwoPi);
+        }
+    }
   }
   // Spectral support of each object: a channel's OTF is nonzero only at
   // differences of two pupil pixels (its autocorrelation).  Each pair of
@@ -347,20 +353,22 @@ int momfbd_plan_create(const momfbd_desc* desc, const float* pupil, const float*
   const int mt = Mp / 16, nk = Mq / 32;
   std::vector<uint4> hZs((size_t)C * Mp * (BP / 8) * 3), hZsT((size_t)C * BP * (Mq / 8) * 3);
   for (int c = 0; c < C; ++c) {
-    for (int m = 0; m < Mp; ++m)
-      for (size_t p8 = 0; p8 < BP / 8; ++p8) {
-        float v[8];
-        for (int e = 0; e < 8; ++e) v[e] = zval(c, m, 8 * p8 + e);
-        put(&hZs[((c * (BP / 32) + p8 / 4) * mt + m / 16) * 192], (int)(p8 % 4) * 16 + m % 16,
-            split8(v));
-      }
-    for (size_t px = 0; px < BP; ++px)
-      for (int m8 = 0; m8 < Mq / 8; ++m8) {
-        float v[8];
-        for (int e = 0; e < 8; ++e) v[e] = zval(c, 8 * m8 + e, px);
-        put(&hZsT[((c * (BP / 16) + px / 16) * nk + m8 / 4) * 192], m8 % 4 * 16 + (int)(px % 16),
-            split8(v));
-      }
+    uint4* run = &hZs[c * (BP / 32) * mt * 192];
+    for (size_t p0 = 0; p0 < BP; p0 += 32)
+      for (int m0 = 0; m0 < Mp; m0 += 16, run += 192)
+        for (int lane = 0; lane < 64; ++lane) {
+          float v[8];
+          for (int e = 0; e < 8; ++e) v[e] = zval(c, m0 + lane % 16, p0 + lane / 16 * 8 + e);
+          put(run, lane, split8(v));
+        }
+    run = &hZsT[c * (BP / 16) * nk * 192];
+    for (size_t p0 = 0; p0 < BP; p0 += 16)
+      for (int m0 = 0; m0 < Mq; m0 += 32, run += 192)
+        for (int lane = 0; lane < 64; ++lane) {
+          float v[8];
+          for (int e = 0; e < 8; ++e) v[e] = zval(c, m0 + lane / 16 * 8 + e, p0 + lane % 16);
+          put(run, lane, split8(v));
+        }
   }
   if (hipGetDevice(&pl->device) != hipSuccess) { delete pl; return MOMFBD_EDEVICE; }
   // the scratch of momfbd_loss_grad_noalloc on this device (a failure here

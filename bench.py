@@ -68,18 +68,18 @@ COPY_WRITE_SCALE = 1.0    # 256 MiB copy: WRITE_SIZE read 262144 KiB
 # per (kernel, N): the knob and, per value of it, (HBM bytes read, written)
 # per launch
 COUNTED_TRAFFIC = {
-    ("adjoint", 64): {"sources_sha1": "0a485a0ac71b", "knob": "xcd_adjoint",
-                      "by_value": {1: (895264574, 94470144), 0: (1094290663, 94470144)}},
-    ("forward", 64): {"sources_sha1": "0a485a0ac71b", "knob": "xcd_forward",
-                      "by_value": {0: (94923414, 405011347), 1: (94926936, 401195873)}},
-    ("object", 64): {"sources_sha1": "380df0fcb916", "knob": "object_pairs_per_thread",
-                     "by_value": {1: (729207247, 32782494)}},
-    ("adjoint", 128): {"sources_sha1": "64d2e7533f56", "knob": "xcd_adjoint",
-                       "by_value": {1: (11984010648, 1511522304), 0: (13304748748, 1511522304)}},
-    ("forward", 128): {"sources_sha1": "64d2e7533f56", "knob": "xcd_forward",
-                       "by_value": {0: (3215663020, 8833985947), 1: (3230672758, 8745003407)}},
-    ("object", 128): {"sources_sha1": "380df0fcb916", "knob": "object_pairs_per_thread",
-                      "by_value": {1: (10901727308, 257959848)}},
+    ("adjoint", 64): {"sources_sha1": "43e02b04e409", "knob": "xcd_adjoint",
+                      "by_value": {1: (895293625, 94470144), 0: (1094380951, 94470144)}},
+    ("forward", 64): {"sources_sha1": "43e02b04e409", "knob": "xcd_forward",
+                      "by_value": {0: (94897868, 404440603), 1: (94900213, 400628168)}},
+    ("object", 64): {"sources_sha1": "cbdbf0cecf85", "knob": "object_pairs_per_thread",
+                     "by_value": {1: (729207388, 32782486)}},
+    ("adjoint", 128): {"sources_sha1": "ad534c1db6d2", "knob": "xcd_adjoint",
+                       "by_value": {1: (11986496049, 1511522304), 0: (13313096194, 1511522304)}},
+    ("forward", 128): {"sources_sha1": "ad534c1db6d2", "knob": "xcd_forward",
+                       "by_value": {0: (3216615743, 8840820484), 1: (3231762912, 8750073519)}},
+    ("object", 128): {"sources_sha1": "cbdbf0cecf85", "knob": "object_pairs_per_thread",
+                      "by_value": {1: (10901719763, 257960210)}},
 }
 
 

@@ -301,8 +301,10 @@ hipError_t run_forward(const momfbd_cnn_s* n, const float* params, const void* D
 }
 
 // The rows (pixels or bursts) of one split of a layer's parameter gradients,
-// a multiple of 32, and the splits: enough blocks of 64 x 64 sums for two on
-// every CU, but at least four stages of 32 rows in each.  The first layer's
+// a multiple of 32, and the splits: enough blocks of 64 x 64 sums for four on
+// every CU, but at least four stages of 32 rows in each (256 bursts of 64 x 64:
+// the convolutions' 62 us with two a CU, 53 with four, k_grad_sum 10.6 and
+// 14.2; the pass 276 and 272).  The first layer's
 // blocks hold all its sums, at least 16 stages each: 512 blocks at 256 bursts
 // of 64 x 64, whose partial sums are 7 MB.
 struct WgradSplit {
@@ -311,7 +313,7 @@ struct WgradSplit {
 WgradSplit wgrad_split(const Layer& L, int l, int K) {
   const int stages = (K + 31) / 32, Mo = L.conv ? L.co : L.n_out;
   const int tiles = (L.K + 64) / 64 * ((Mo + 63) / 64);
-  int splits = l == 0 ? (stages + 15) / 16 : std::min((stages + 3) / 4, std::max(1, 512 / tiles));
+  int splits = l == 0 ? (stages + 15) / 16 : std::min((stages + 3) / 4, std::max(1, 1024 / tiles));
   splits = std::max(1, std::min(splits, 512));
   const int rows = (stages + splits - 1) / splits * 32;
   return WgradSplit{rows, (K + rows - 1) / rows};

@@ -636,10 +636,10 @@ __global__ __launch_bounds__(256) void k_dense_dx(int M, int N, int K, int kchun
 // a thread takes two rows of eight columns and stores the eight pairs, so the
 // matrix operands' eight consecutive k are one 16-byte read.  A block is a 64
 // x 64 tile, wave (a, b) 32 x 32 of it, in stages of 32 rows, two of
-// them in flight.  At 256 bursts of 64 x 64 the three convolutions take 24, 23
-// and 15 us: about 1 us a stage, most of it the instructions that gather and
-// pair the rows (blocks of one row range kept on one XCD: 21, 22, 14 us, and
-// the dense layers, of few row ranges, 15 instead of 7).
+// them in flight.  At 256 bursts of 64 x 64 the three convolutions take 20, 19
+// and 14 us with four blocks a CU, most of it the instructions that gather and
+// pair the rows (24, 23 and 15 with two; then, blocks of one row range kept on
+// one XCD: 21, 22, 14, and the dense layers, of few row ranges, 15 instead of 7).
 template <int CI>
 __global__ __launch_bounds__(256) void k_wgrad(int M, int N, int K, int rows, int H,
                                                const uint16_t* __restrict__ P,

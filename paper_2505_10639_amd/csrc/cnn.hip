@@ -310,21 +310,27 @@ hipError_t run_forward(const momfbd_cnn_s* n, const float* params, const void* D
 struct WgradSplit {
   int rows, splits;
 };
+// the most splits of a layer's K rows; never fewer for a larger K
+int wgrad_max_splits(const Layer& L, int l, long K) {
+  const long stages = (K + 31) / 32;
+  const int Mo = L.conv ? L.co : L.n_out, tiles = (L.K + 64) / 64 * ((Mo + 63) / 64);
+  const long splits =
+      l == 0 ? (stages + 15) / 16 : std::min((stages + 3) / 4, std::max(1L, 1024L / tiles));
+  return (int)std::max(1L, std::min(splits, 512L));
+}
 WgradSplit wgrad_split(const Layer& L, int l, int K) {
-  const int stages = (K + 31) / 32, Mo = L.conv ? L.co : L.n_out;
-  const int tiles = (L.K + 64) / 64 * ((Mo + 63) / 64);
-  int splits = l == 0 ? (stages + 15) / 16 : std::min((stages + 3) / 4, std::max(1, 1024 / tiles));
-  splits = std::max(1, std::min(splits, 512));
+  const int stages = (K + 31) / 32, splits = wgrad_max_splits(L, l, K);
   const int rows = (stages + splits - 1) / splits * 32;
   return WgradSplit{rows, (K + rows - 1) / rows};
 }
 
-// floats of every layer's split sums at `B` bursts
-long wgrad_floats(const std::vector<Layer>& layers, int B) {
+// floats that hold every layer's split sums at any batch up to `batch_max`
+long wgrad_floats(const std::vector<Layer>& layers, int batch_max) {
   long n = 0;
   for (size_t l = 0; l < layers.size(); ++l) {
     const Layer& L = layers[l];
-    n += (long)wgrad_split(L, (int)l, (int)(B * L.rows)).splits * (L.conv ? L.co : L.n_out) * (L.K + 1);
+    n += (long)wgrad_max_splits(L, (int)l, batch_max * L.rows) * (L.conv ? L.co : L.n_out) *
+         (L.K + 1);
   }
   return n;
 }
@@ -449,11 +455,9 @@ int momfbd_cnn_create(int N, int J, int M, int batch_max, const float* mode_scal
     part = std::max(part, (size_t)Bm * L.rows * L.K);
   }
   n->part_floats = part;
-  // split sums of the parameter gradients, at the batch that needs most
-  long sums = 0;
-  for (int B = 1; B <= batch_max; ++B) sums = std::max(sums, wgrad_floats(n->layers, B));
+  // split sums of the parameter gradients
   n->o_part = o;
-  o = al256(o + (size_t)sums * sizeof(float));
+  o = al256(o + (size_t)wgrad_floats(n->layers, batch_max) * sizeof(float));
   n->o_dz = o;
   o = al256(o + max_dz * sizeof(uint16_t));
   n->o_dz2 = o;

@@ -434,8 +434,8 @@ typedef struct {
   int xcd_forward;              /* 1: units of a patch-object on one XCD (L2)   */
   int xcd_adjoint;              /* same for the adjoint kernel                  */
   int object_pairs_per_thread;  /* 1, 2 or 4 frequency pairs per thread         */
-  int grad_waves;               /* gradient contraction: 4 waves x 4, 3 or 2
-                                   row tiles, or 8 waves x 2 row tiles per
+  int grad_waves;               /* gradient contraction: 4 waves x 3 or 2 row
+                                   tiles, or 8 waves x 2 row tiles per
                                    workgroup; every wave owns its rows, and
                                    each basis chunk staged in LDS serves all
                                    the workgroup's rows                       */
@@ -445,25 +445,26 @@ typedef struct {
                                    pixel chunks (get_tuning reports the count
                                    in use)                                    */
   int grad_row_tiles;           /* row tiles of 16 (patch, frame) rows per
-                                   wave: 4, 3 or 2 with 4 waves (fewer: more,
-                                   smaller workgroups, each basis chunk
-                                   serving fewer rows), 2 with 8 waves; 0 on
-                                   input leaves it open: with 4 waves 4 up to
-                                   256 rows and 2 beyond (as get_tuning
-                                   reports), and few rows x modes run a kernel
-                                   that stages nothing, with the same sums  */
+                                   wave: 3 or 2 with 4 waves, 2 with 8.  0 or 4
+                                   with 4 waves leaves the shape open: 2 row
+                                   tiles, and for few rows x modes a kernel
+                                   that stages nothing, with the same sums at
+                                   equal splits.  get_tuning reports an open
+                                   shape as 4                                 */
   int phase_col_tiles;          /* phase contraction (Eq. wavefront): 16-column
                                    tiles of (patch, frame) columns per
                                    workgroup, whose coefficients it stages in
                                    LDS, each basis part read serving them all */
-  int phase_waves;              /* and its waves: 8 x 8, 4 x 8 or 8 x 16
-                                   (tiles x waves) while the staged
-                                   coefficients fit 128 KB of LDS; 0, 0 on
-                                   input leaves it open: 8 x 8 up to 128
-                                   columns where it fits (run by a kernel that
-                                   stages nothing, with the same sums), else
-                                   4 x 8 (get_tuning reports the shape;
-                                   set_tuning also takes it as reported)      */
+  int phase_waves;              /* and its waves: 4 x 8 or 8 x 16 (tiles x
+                                   waves) while the staged coefficients fit
+                                   128 KB of LDS (8 x 16: up to 160 modes).
+                                   0, 0 leaves the shape open: 4 x 8, and up to
+                                   128 columns a kernel that stages nothing,
+                                   with the same sums.  get_tuning reports an
+                                   open shape as 8 x 8, from 161 modes on as
+                                   2 x 4, and set_tuning takes it as reported,
+                                   so that a tuning given back restores what
+                                   ran                                        */
   int object_fused;             /* 1: the forward transforms and the Wiener
                                    object and loss (Eqs. object_optimization,
                                    loss_momfbd) in one launch, a workgroup per

@@ -6,6 +6,7 @@
 
 #include "contract_mfma.h"
 #include "internal.h"
+#include "schedule.h"
 
 namespace mfbd {
 namespace {
@@ -93,14 +94,13 @@ hipError_t launch_grad_k(const Dims& d, int zc, int splits, const uint4* Zs, con
   return hipGetLastError();
 }
 
-constexpr int kCus = 256;
-
 template <int MT, int CS>
 hipError_t launch_grad_cs(const Dims& d, int zc, int splits, const uint4* Zs, const float* gphi,
                           float* grad, float* part, hipStream_t s) {
   if (d.grad_waves == 8) return launch_grad_k<MT, 2, 8, CS>(d, zc, splits, Zs, gphi, grad, part, s);
   switch (grad_row_tiles_of(d)) {
-    case 2: {
+    case 3: return launch_grad_k<MT, 3, 4, CS>(d, zc, splits, Zs, gphi, grad, part, s);
+    default: {
       // at most one block per CU: 133 us with two chunks of loads in flight
       // against 160 with one at 3072 rows x 150 modes of four 128 x 128 bases;
       // with more blocks the registers cost occupancy (11 532 rows x 66 modes
@@ -110,8 +110,6 @@ hipError_t launch_grad_cs(const Dims& d, int zc, int splits, const uint4* Zs, co
         return launch_grad_k<MT, 2, 4, CS, 2>(d, zc, splits, Zs, gphi, grad, part, s);
       return launch_grad_k<MT, 2, 4, CS>(d, zc, splits, Zs, gphi, grad, part, s);
     }
-    case 3: return launch_grad_k<MT, 3, 4, CS>(d, zc, splits, Zs, gphi, grad, part, s);
-    default: return launch_grad_k<MT, 4, 4, CS>(d, zc, splits, Zs, gphi, grad, part, s);
   }
 }
 
@@ -125,52 +123,6 @@ hipError_t launch_grad_t(const Dims& d, int splits, const uint4* Zs, const float
 }
 
 }  // namespace
-
-// The schedule of the gradient when the plan leaves it open (4 waves, row
-// tiles 0).  Few rows: the kernel that stages nothing (k_grad_rows), whose
-// basis reads grow with rows x mode tiles and which needs no block of 128
-// rows to be full: 11.6 against 12.4 us at 2700 rows x 3 tiles (64 x 64), 18
-// against 21.5 at 1000 x 10, 29 against 73 at 441 x 5 (128 x 128, three
-// bases), but 27.8 against 20 at 5400 x 6 and 26.3 against 25.7 at 1944 x 8.
-constexpr long kFewRowTiles = 12000;
-static bool grad_few_rows(const Dims& d) {
-  return d.grad_waves != 8 && d.grad_rt == 0 &&
-         (long)d.P * d.J * ((d.M + 15) / 16) <= kFewRowTiles;
-}
-
-int grad_splits_staged(long blocks, int nchunk) {
-  // a block for every CU, as long as every split keeps at least 4 chunks of
-  // 32 pixels to pipeline through its LDS stages (2 row tiles x 4 waves, 5400
-  // rows x 88 modes at 64 x 64: 21 us at 8 splits of 4 chunks, 22.6 at 4;
-  // 11 532 x 66: 32.4 at 4 splits, 33.2 at 8)
-  int s = 1;
-  while (s < kMaxGradSplits && blocks * s < kCus && nchunk / (2 * s) >= 4) s *= 2;
-  return s;
-}
-
-int grad_splits_auto(const Dims& d) {
-  const int R = d.P * d.J, W = d.grad_waves == 8 ? 8 : 4;
-  const int zc = d.zc > 0 ? d.zc : d.C;
-  const int nchunk = zc * d.bandpix() / 32;
-  const long rows = 16L * grad_row_tiles_of(d) * W, blocks = (R + rows - 1) / rows;
-  if (grad_few_rows(d) || R <= 256) {
-    // at least 8 chunks to a split
-    int s = 1;
-    while (s < kMaxGradSplits && blocks * s < 512 && nchunk / (2 * s) >= 8) s *= 2;
-    return s;
-  }
-  return grad_splits_staged(blocks, nchunk);
-}
-
-int grad_splits_of(const Dims& d) { return d.grad_splits > 0 ? d.grad_splits : grad_splits_auto(d); }
-
-// (open: 4 where one block of 256 rows holds them all, else 2, whose blocks of
-// 128 rows were the fastest staged shape at every size measured)
-int grad_row_tiles_of(const Dims& d) {
-  if (d.grad_waves == 8) return 2;
-  if (d.grad_rt > 0) return d.grad_rt;
-  return (long)d.P * d.J <= 256 ? 4 : 2;
-}
 
 hipError_t launch_grad(const Dims& d, const uint4* Zs, const float* gphi, float* grad,
                        float* part, hipStream_t s, const LossSum* ls) {
@@ -206,10 +158,8 @@ hipError_t launch_grad(const Dims& d, const uint4* Zs, const float* gphi, float*
   return hipGetLastError();
 }
 
-// Phase blocks: 64 columns and 8 waves, unless the plan selects 128 columns
-// with 8 or 16 waves (their staged coefficients must fit 128 KB of LDS).  A
-// block takes a quarter of the band's pixel tiles, fewer where that leaves CUs
-// idle (at least one per wave): 16.4 against 28 us at 441 columns x 77 modes
+// A block takes a quarter of the band's pixel tiles, fewer where that leaves
+// CUs idle (at least one per wave): 16.4 against 28 us at 441 columns x 77 modes
 // (128 x 128, three bases); going on to 512 blocks and more cost up to a
 // quarter at the larger sizes, where every block stages its coefficients anew.
 template <int CT, int W>
@@ -228,44 +178,17 @@ hipError_t launch_phase_ct(const Dims& d, const float* alpha, const uint4* ZsT, 
   return hipGetLastError();
 }
 
-bool phase_shape_fits(int ct, int waves, int Mq) {
-  const bool listed = (ct == 8 && waves == 8) || (ct == 4 && waves == 8) || (ct == 8 && waves == 16);
-  return listed && contract::phase_lds_bytes(ct, Mq) <= 128 * 1024;
-}
-
-// (open: one block of 128 columns where it holds them all, else 64, the faster
-// at every larger size measured: 9.7 against 12.6 us at 2700 columns x 44 modes
-// and 26.7 against 29.5 at 11 532 x 66 (64 x 64), 97 against 129 at 3072 x 150
-// (128 x 128, four bases); 64 columns fit for every mode count)
-void phase_shape_of(const Dims& d, int Mq, int* ct, int* waves) {
-  if (d.phase_ct > 0 && phase_shape_fits(d.phase_ct, d.phase_waves, Mq)) {
-    *ct = d.phase_ct;
-    *waves = d.phase_waves;
-    return;
-  }
-  *ct = (long)d.P * d.J <= 128 && phase_shape_fits(8, 8, Mq) ? 8 : 4;
-  *waves = 8;
-}
-
-// Columns up to which an open schedule takes the kernel that stages nothing:
-// 3.1 against 5.1 us at 8 columns x 44 modes, 4.3 against 12.3 at 128 x 66 (64
-// x 64), 9 against 16.2 at 120 x 150 (128 x 128), but 12.8 against 7.9 at 200 x
-// 66 (96 x 96, three bases).
-constexpr int kFewCols = 128;
-
 hipError_t launch_phase(const Dims& d, const float* alpha, const uint4* ZsT, int Mq,
                         const float* thetat, float* phi, hipStream_t s) {
   const int R = d.P * d.J;
-  if (d.phase_ct == 0 && R <= kFewCols) {
+  const PhaseShape shape = phase_shape_of(d);
+  if (shape.few) {
     const int zc = d.zc > 0 ? d.zc : d.C;
     hipLaunchKernelGGL(k_phase_few<1>, dim3(zc * (d.bandpix() / 64), (R + 15) / 16), dim3(256), 0,
                        s, R, d.J, d.C, zc, d.M, Mq, d.bandpix(), ZsT, thetat, alpha, phi);
     return hipGetLastError();
   }
-  int ct = 0, w = 0;
-  phase_shape_of(d, Mq, &ct, &w);
-  if (ct == 8 && w == 16) return launch_phase_ct<8, 16>(d, alpha, ZsT, Mq, thetat, phi, s);
-  if (ct == 8) return launch_phase_ct<8, 8>(d, alpha, ZsT, Mq, thetat, phi, s);
+  if (shape.ct == 8) return launch_phase_ct<8, 16>(d, alpha, ZsT, Mq, thetat, phi, s);
   return launch_phase_ct<4, 8>(d, alpha, ZsT, Mq, thetat, phi, s);
 }
 

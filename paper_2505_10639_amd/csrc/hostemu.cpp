@@ -12,6 +12,7 @@
 #include "ops128.h"
 #include "ops64.h"
 #include "ops96.h"
+#include "schedule.h"
 
 using namespace mfbd;
 using namespace mfbd::n64;
@@ -686,6 +687,33 @@ void emu96_unit(const float* A, const float* ph, float kappa, const float* G_hal
       gphi[(2 * i + b) * 48 + q] = pk.x * gp.y - pk.y * gp.x;
     }
   }
+}
+
+// A schedule set on a plan of `dims` (N, P, C, J, M, bases; every plan value
+// open), as get_tuning then reports it and as it launches: the gradient's kind
+// (0 nothing staged), waves, row tiles and splits, the phase's kind, column
+// tiles and waves.  Returns 0 where the schedule is refused.
+int emu_schedule(const int* dims, const int* set, int* got, int* runs) {
+  mfbd::Dims d{dims[0], dims[1], dims[2], 1, dims[3], dims[4]};
+  d.zc = dims[5];
+  const int Mq = (d.M + 31) / 32 * 32;
+  if (set) {
+    momfbd_tuning t;
+    std::memcpy(&t, set, sizeof t);
+    if (!schedule_set(t, Mq, d)) return 0;
+  }
+  const momfbd_tuning r = schedule_get(d, Mq);
+  std::memcpy(got, &r, sizeof r);
+  const bool few = grad_few_rows(d);
+  runs[0] = few ? 0 : 1;
+  runs[1] = few ? 0 : d.grad_waves;
+  runs[2] = few ? 0 : grad_row_tiles_of(d);
+  runs[3] = grad_splits_of(d);
+  const PhaseShape ph = phase_shape_of(d);
+  runs[4] = ph.few ? 0 : 1;
+  runs[5] = ph.few ? 0 : ph.ct;
+  runs[6] = ph.few ? 0 : ph.waves;
+  return 1;
 }
 
 }  // extern "C"

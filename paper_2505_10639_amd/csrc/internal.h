@@ -28,11 +28,11 @@ struct Dims {
   // order of the forward / adjoint grids, frequency pairs per thread of the
   // object kernel, waves per row tile of the gradient contraction and the
   // number of blocks its pixel sum is split over (0: grad_splits_auto) and
-  // its row tiles per wave (0: open, see grad_row_tiles_of; 4, 3 or 2 with 4
-  // waves; 8 waves always take 2)
+  // its row tiles per wave (0: open; 3 or 2 with 4 waves; 8 waves always take
+  // 2); the rules are in schedule.h
   int xcd_fwd = 0, xcd_adj = 1, obj_ppt = 1, grad_waves = 4, grad_splits = 0, grad_rt = 0;
   // the phase contraction's block: 16-column tiles and waves per workgroup
-  // (0, 0: open, see phase_shape_of and launch_phase)
+  // (0, 0: open)
   int phase_ct = 0, phase_waves = 0;
   // the object pass in the forward launch (k_fwdobj64) where it applies
   // (fuse_ok, set at plan creation: 64x64 patches, at most 12 units per
@@ -303,16 +303,8 @@ struct GroupArgs {
 };
 
 // The gradient contraction's pixel sum may be split over up to this many
-// blocks per row tile; grad_splits_of gives the plan's split count.
+// blocks per row tile (schedule.h).
 constexpr int kMaxGradSplits = 8;
-int grad_splits_auto(const Dims& d);
-int grad_splits_staged(long blocks, int nchunk);
-int grad_splits_of(const Dims& d);
-int grad_row_tiles_of(const Dims& d);
-// The phase contraction's block in use (column tiles, waves), and whether a
-// selectable one (8 x 8, 4 x 8 or 8 x 16) fits the LDS for Mq staged modes.
-void phase_shape_of(const Dims& d, int Mq, int* ct, int* waves);
-bool phase_shape_fits(int ct, int waves, int Mq);
 
 size_t workspace_bytes(const Dims& d);
 Workspace carve_workspace(const Dims& d, void* base);

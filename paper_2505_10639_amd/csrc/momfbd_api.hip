@@ -13,6 +13,7 @@
 #include "bf16split.h"
 #include "internal.h"
 #include "momfbd.h"
+#include "schedule.h"
 
 using namespace mfbd;
 
@@ -411,53 +412,14 @@ int momfbd_plan_destroy(momfbd_plan plan) {
   return MOMFBD_OK;
 }
 
-static bool tuning_ok(const momfbd_tuning* t) {
-  return t && (t->xcd_forward == 0 || t->xcd_forward == 1) &&
-         (t->xcd_adjoint == 0 || t->xcd_adjoint == 1) &&
-         (t->object_pairs_per_thread == 1 || t->object_pairs_per_thread == 2 ||
-          t->object_pairs_per_thread == 4) &&
-         (t->grad_waves == 4 || t->grad_waves == 8) &&
-         (t->grad_splits == 0 || t->grad_splits == 1 || t->grad_splits == 2 ||
-          t->grad_splits == 4 || t->grad_splits == 8) &&
-         (t->grad_row_tiles == 0 ||
-          (t->grad_waves == 4 ? t->grad_row_tiles >= 2 && t->grad_row_tiles <= 4
-                              : t->grad_row_tiles == 2)) &&
-         (t->object_fused == 0 || t->object_fused == 1);
-}
-
 int momfbd_plan_set_tuning(momfbd_plan plan, const momfbd_tuning* t) {
-  if (!plan || !tuning_ok(t)) return MOMFBD_EINVAL;
-  // the automatic phase block, as get_tuning reports it, is accepted too
-  Dims dauto = plan->d;
-  dauto.phase_ct = dauto.phase_waves = 0;
-  int act = 0, awaves = 0;
-  phase_shape_of(dauto, plan->Mq, &act, &awaves);
-  const bool phase_auto = (t->phase_col_tiles == 0 && t->phase_waves == 0) ||
-                          (t->phase_col_tiles == act && t->phase_waves == awaves);
-  if (!phase_auto && !phase_shape_fits(t->phase_col_tiles, t->phase_waves, plan->Mq))
-    return MOMFBD_EINVAL;
-  plan->d.phase_ct = phase_auto ? 0 : t->phase_col_tiles;
-  plan->d.phase_waves = phase_auto ? 0 : t->phase_waves;
-  plan->d.xcd_fwd = t->xcd_forward;
-  plan->d.xcd_adj = t->xcd_adjoint;
-  plan->d.obj_ppt = t->object_pairs_per_thread;
-  plan->d.grad_waves = t->grad_waves;
-  plan->d.grad_splits = t->grad_splits;
-  plan->d.grad_rt = t->grad_waves == 8 ? 0 : t->grad_row_tiles;
-  plan->d.fuse_obj = t->object_fused;
+  if (!plan || !t || !schedule_set(*t, plan->Mq, plan->d)) return MOMFBD_EINVAL;
   return MOMFBD_OK;
 }
 
 int momfbd_plan_get_tuning(momfbd_plan plan, momfbd_tuning* t) {
   if (!plan || !t) return MOMFBD_EINVAL;
-  t->xcd_forward = plan->d.xcd_fwd;
-  t->xcd_adjoint = plan->d.xcd_adj;
-  t->object_pairs_per_thread = plan->d.obj_ppt;
-  t->grad_waves = plan->d.grad_waves;
-  t->grad_splits = grad_splits_of(plan->d);
-  t->grad_row_tiles = grad_row_tiles_of(plan->d);
-  phase_shape_of(plan->d, plan->Mq, &t->phase_col_tiles, &t->phase_waves);
-  t->object_fused = fused_object(plan->d) ? 1 : 0;
+  *t = schedule_get(plan->d, plan->Mq);
   return MOMFBD_OK;
 }
 
@@ -867,20 +829,20 @@ int momfbd_plan_autotune(momfbd_plan plan, const float* alpha, const void* D, co
   // far only when at least 1% faster, so that timing noise between
   // near-equal schedules does not decide (the XCD-grouped orders read less
   // from HBM at equal speed).
-  // The gradient's shape is one knob: the open schedule, 4 waves with 4, 3 or
-  // 2 row tiles, or 8 waves with 2 (each with its automatic split count); its split count
-  // is the next knob, starting from the automatic one for the chosen shape,
+  // The gradient's shape is one knob: the open schedule, 4 waves with 3 or 2
+  // row tiles, or 8 waves with 2 (each with its automatic split count); its
+  // split count is the next knob, starting from the automatic one for the chosen shape,
   // the others following in increasing order.  After the last knob, one
   // whole evaluation under the chosen schedules leaves the loss and
   // gradient outputs of that schedule.  Knobs 0-5 time the adjoint, the
   // forward, the object kernel, (3, 4) the gradient contraction and (5) the
   // phase contraction, whose candidates are its open schedule and the
-  // selectable blocks (8 x 8, 4 x 8, 8 x 16 tiles x waves) that fit; knob 6, where
+  // selectable blocks (4 x 8, 8 x 16 tiles x waves) that fit; knob 6, where
   // the plan allows it, the forward and object pass in two launches (the
   // default, under the schedules chosen for them) against one.
   constexpr int kRounds = 3;
-  static const int kShapes[5][2] = {{4, 0}, {4, 4}, {4, 3}, {4, 2}, {8, 0}};
-  static const int kPhaseShapes[4][2] = {{0, 0}, {8, 8}, {4, 8}, {8, 16}};
+  static const int kShapes[4][2] = {{4, 0}, {4, 3}, {4, 2}, {8, 0}};
+  static const int kPhaseShapes[3][2] = {{0, 0}, {4, 8}, {8, 16}};
   auto set_knob = [&](int k, int v) {
     switch (k) {
       case 0: plan->d.xcd_adj = v; break;
@@ -900,9 +862,9 @@ int momfbd_plan_autotune(momfbd_plan plan, const float* alpha, const void* D, co
     }
   };
   const Dims keep_d = plan->d;
-  std::vector<int> values[7] = {{1, 0}, {0, 1}, {1, 2, 4}, {0, 1, 2, 3, 4}, {}, {0}, {}};
+  std::vector<int> values[7] = {{1, 0}, {0, 1}, {1, 2, 4}, {0, 1, 2, 3}, {}, {0}, {}};
   if (plan->d.fuse_ok) values[6] = {0, 1};
-  for (int v = 1; v < 4; ++v)
+  for (int v = 1; v < 3; ++v)
     if (phase_shape_fits(kPhaseShapes[v][0], kPhaseShapes[v][1], plan->Mq)) values[5].push_back(v);
   for (int k = 0; k < 7 && st == MOMFBD_OK; ++k) {
     if (k == 6 && values[6].empty()) break;
@@ -1238,7 +1200,7 @@ int momfbd_group_lbfgs_rounds(momfbd_group g, int rounds, void* stream) {
 }
 
 int momfbd_group_set_tuning(momfbd_group g, const momfbd_tuning* t) {
-  if (!g || !tuning_ok(t) || t->grad_waves != 4) return MOMFBD_EINVAL;
+  if (!g || !t || !schedule_values_ok(*t) || t->grad_waves != 4) return MOMFBD_EINVAL;
   g->xcd_fwd = t->xcd_forward;
   g->xcd_adj = t->xcd_adjoint;
   g->grad_rt = t->grad_row_tiles == 0 ? group_default_rt(g->mt_max)

@@ -99,9 +99,10 @@ class Plan:
                    grad_splits=0, grad_row_tiles=0, phase_col_tiles=0, phase_waves=0,
                    object_fused=0):
         """Launch schedules (see momfbd_tuning); grad_splits 0 is automatic,
-        grad_row_tiles 0 leaves the row tiles open, phase_col_tiles and
-        phase_waves 0 the phase block, object_fused 1 the
-        forward and object pass in one launch where the plan allows it."""
+        grad_row_tiles 0 leaves the gradient's shape open, phase_col_tiles and
+        phase_waves 0 the phase block's (what tuning() reports restores either),
+        object_fused 1 the forward and object pass in one launch where the plan
+        allows it."""
         _lib.momfbd_plan_set_tuning(self.handle, xcd_forward, xcd_adjoint,
                                     object_pairs_per_thread, grad_waves, grad_splits,
                                     grad_row_tiles, phase_col_tiles, phase_waves, object_fused)

@@ -94,6 +94,15 @@ hipError_t launch_grad_k(const Dims& d, int zc, int splits, const uint4* Zs, con
   return hipGetLastError();
 }
 
+// Whether the accumulators of MT mode tiles leave registers for two chunks in
+// flight.  Beyond, the two-chunk instances spill up to 100 registers (at 16
+// tiles of separate bases none, and still lose): 3072 rows of 64 x 64, one
+// basis: 29 us against 35 at 224 modes, 30 against 42 at 240, 34 against 35 at
+// 256; three channels 35 against 39, 36 against 44, 38 against 51; two bases 39
+// against 47 at 240, 40 against 42 at 256, but at 224 39 against 38.
+template <int MT, int CS>
+constexpr bool kTwoChunksFit = MT <= (CS == 1 ? 14 : 13);
+
 template <int MT, int CS>
 hipError_t launch_grad_cs(const Dims& d, int zc, int splits, const uint4* Zs, const float* gphi,
                           float* grad, float* part, hipStream_t s) {
@@ -105,9 +114,11 @@ hipError_t launch_grad_cs(const Dims& d, int zc, int splits, const uint4* Zs, co
       // against 160 with one at 3072 rows x 150 modes of four 128 x 128 bases;
       // with more blocks the registers cost occupancy (11 532 rows x 66 modes
       // at 64 x 64: 34.5 against 32.4)
-      const long blocks = ((long)d.P * d.J + 127) / 128 * splits;
-      if (blocks <= kCus)
-        return launch_grad_k<MT, 2, 4, CS, 2>(d, zc, splits, Zs, gphi, grad, part, s);
+      if constexpr (kTwoChunksFit<MT, CS>) {
+        const long blocks = ((long)d.P * d.J + 127) / 128 * splits;
+        if (blocks <= kCus)
+          return launch_grad_k<MT, 2, 4, CS, 2>(d, zc, splits, Zs, gphi, grad, part, s);
+      }
       return launch_grad_k<MT, 2, 4, CS>(d, zc, splits, Zs, gphi, grad, part, s);
     }
   }

@@ -458,9 +458,10 @@ typedef struct {
   int phase_waves;              /* and its waves: 4 x 8 or 8 x 16 (tiles x
                                    waves) while the staged coefficients fit
                                    128 KB of LDS (8 x 16: up to 160 modes).
-                                   0, 0 leaves the shape open: 4 x 8, and up to
-                                   128 columns a kernel that stages nothing,
-                                   with the same sums.  get_tuning reports an
+                                   0, 0 leaves the shape open: 4 x 8, or 3 x 8
+                                   for many columns of more than 192 modes, and
+                                   up to 128 columns a kernel that stages
+                                   nothing, with the same sums.  get_tuning reports an
                                    open shape as 8 x 8, from 161 modes on as
                                    2 x 4, and set_tuning takes it as reported,
                                    so that a tuning given back restores what

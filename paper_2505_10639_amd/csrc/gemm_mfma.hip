@@ -192,7 +192,7 @@ hipError_t launch_phase_ct(const Dims& d, const float* alpha, const uint4* ZsT, 
 hipError_t launch_phase(const Dims& d, const float* alpha, const uint4* ZsT, int Mq,
                         const float* thetat, float* phi, hipStream_t s) {
   const int R = d.P * d.J;
-  const PhaseShape shape = phase_shape_of(d);
+  const PhaseShape shape = phase_shape_of(d, Mq);
   if (shape.few) {
     const int zc = d.zc > 0 ? d.zc : d.C;
     hipLaunchKernelGGL(k_phase_few<1>, dim3(zc * (d.bandpix() / 64), (R + 15) / 16), dim3(256), 0,
@@ -200,6 +200,7 @@ hipError_t launch_phase(const Dims& d, const float* alpha, const uint4* ZsT, int
     return hipGetLastError();
   }
   if (shape.ct == 8) return launch_phase_ct<8, 16>(d, alpha, ZsT, Mq, thetat, phi, s);
+  if (shape.ct == 3) return launch_phase_ct<3, 8>(d, alpha, ZsT, Mq, thetat, phi, s);
   return launch_phase_ct<4, 8>(d, alpha, ZsT, Mq, thetat, phi, s);
 }
 

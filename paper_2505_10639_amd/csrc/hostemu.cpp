@@ -709,7 +709,7 @@ int emu_schedule(const int* dims, const int* set, int* got, int* runs) {
   runs[1] = few ? 0 : d.grad_waves;
   runs[2] = few ? 0 : grad_row_tiles_of(d);
   runs[3] = grad_splits_of(d);
-  const PhaseShape ph = phase_shape_of(d);
+  const PhaseShape ph = phase_shape_of(d, Mq);
   runs[4] = ph.few ? 0 : 1;
   runs[5] = ph.few ? 0 : ph.ct;
   runs[6] = ph.few ? 0 : ph.waves;

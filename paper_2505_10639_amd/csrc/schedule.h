@@ -15,6 +15,7 @@
 namespace mfbd {
 
 constexpr int kCus = 256;
+constexpr size_t kLdsPerCu = 160 * 1024;
 
 // ---- gradient
 // Few rows under an open schedule (4 waves, row tiles 0) take the kernel that
@@ -64,21 +65,30 @@ inline int grad_splits_of(const Dims& d) {
 }
 
 // ---- phase
-// Open: 64 columns and 8 waves, the faster at every size beyond kFewCols
+// Open: 64 columns and 8 waves, the faster at nearly every size beyond kFewCols
 // columns: 9.7 against 12.6 us (128 columns, 8 waves) at 2700 columns x 44 modes,
 // 26.7 against 29.5 at 11 532 x 66 (64 x 64), 97 against 129 at 3072 x 150 (128 x
-// 128, four bases); 64 columns fit for every mode count.  Up to kFewCols columns
-// the kernel that stages nothing: 3.1 against 5.1 us at 8 columns x 44 modes, 4.3
-// against 12.3 at 128 x 66 (64 x 64), 9 against 16.2 at 120 x 150 (128 x 128), but
-// 12.8 against 7.9 at 200 x 66 (96 x 96, three bases).
+// 128, four bases); they fit for every mode count.  From 193 modes on they take
+// more than half of a CU's LDS, and a launch of many blocks does better with
+// two blocks of 48 columns there: 200 modes of 64 x 64, 3072 columns 19.2 against
+// 28.6 us (two bases 25.5 against 37.0), 11 532 columns 49 against 61; 1536 columns
+// of 128 x 128, two bases, 47 against 60; but 1000 columns of 64 x 64, two bases,
+// 17.5 against 14.3, and 800 of 96 x 96, one basis, 22.3 against 17.7.
+// Up to kFewCols columns the kernel that stages nothing: 3.1 against 5.1 us at 8
+// columns x 44 modes, 4.3 against 12.3 at 128 x 66 (64 x 64), 9 against 16.2 at 120
+// x 150 (128 x 128), but 12.8 against 7.9 at 200 x 66 (96 x 96, three bases).
 constexpr int kFewCols = 128;
 struct PhaseShape {
   bool few;        // nothing staged (ct, waves unused)
   int ct, waves;   // 16-column tiles and waves per workgroup
 };
-inline PhaseShape phase_shape_of(const Dims& d) {
+inline PhaseShape phase_shape_of(const Dims& d, int Mq) {
   if (d.phase_ct > 0) return PhaseShape{false, d.phase_ct, d.phase_waves};
-  return PhaseShape{(long)d.P * d.J <= kFewCols, 4, 8};
+  const long R = (long)d.P * d.J, zc = d.zc > 0 ? d.zc : d.C;
+  if (R <= kFewCols) return PhaseShape{true, 0, 0};
+  const bool one_per_cu = 2 * contract::phase_lds_bytes(4, Mq) > kLdsPerCu;
+  const long blocks = 4 * zc * ((R + 63) / 64);   // a quarter of the band each
+  return PhaseShape{false, one_per_cu && blocks >= 3 * kCus / 4 ? 3 : 4, 8};
 }
 
 // A shape that can be selected for Mq padded modes: its staged coefficients

@@ -40,7 +40,7 @@ def test_reported_tuning_round_trip():
 
 @pytest.mark.parametrize("P,J,M", [(1, 1, 1), (8, 16, 47), (43, 3, 20), (8, 16, 160), (43, 3, 160),
                                    (8, 16, 161), (43, 3, 256), (90, 10, 208), (90, 10, 224),
-                                   (90, 10, 240)])
+                                   (90, 10, 240), (200, 16, 200), (200, 16, 256)])
 def test_selected_shapes_equal_open(P, J, M):
     plan = make(P, J, M)
     dev = plan.device

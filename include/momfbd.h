@@ -204,6 +204,8 @@ typedef struct {
  *   filters  host [K]
  *   obj      [P][K][N][N] float (device), as momfbd_object_estimate
  *   H        [P][K][N][N/2+1] float (device) receives the filters, or NULL
+ * obj is written last: it may overlap the inputs.  The forward and object pass
+ * run in two launches whatever the plan's object_fused (same results).
  * Errors: EINVAL (NULL, unknown kind, f_hi <= f_lo, diff_limit <= 0,
  * eta < 0), EWORKSPACE, EDEVICE. */
 int momfbd_object_filtered(momfbd_plan plan, const float* alpha, const void* D,

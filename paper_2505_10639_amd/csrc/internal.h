@@ -209,6 +209,50 @@ __device__ __forceinline__ double object_pair(int f2, int p, int k, int C, int J
   return loss;
 }
 
+// Sums of frequency pair f2 of a plane whose object takes the Loefdahl-Scharmer
+// filter: N, sum w |S|^2 (no gamma) and E as object_pair, but reading S beyond
+// the object's support too (the filter is defined by the OTFs as they are).
+template <int NN>
+__device__ __forceinline__ Acc2 scharmer_sums(int f2, int p, int k, int C, int J, const ChanTab& ct,
+                                              const float2* __restrict__ D,
+                                              const float* __restrict__ weights,
+                                              const float2* __restrict__ S) {
+  constexpr int kUnitF2 = NN * (NN / 2 + 1);
+  Acc2 a;
+  for (int i = 0; i < 2; ++i) a.nr[i] = a.ni[i] = a.q[i] = a.e[i] = 0.0;
+  const int c0 = ct.obj_first[k], c1 = ct.obj_first[k + 1];
+  for (int ci = c0; ci < c1; ++ci) {
+    const int c = ct.obj_chans[ci];
+    const size_t at = ((size_t)(p * C + c) * J) * kUnitF2 + 2 * f2;
+    const float4* Dc = reinterpret_cast<const float4*>(D + at);
+    const float4* Sc = reinterpret_cast<const float4*>(S + at);
+    const float* wc = weights ? weights + c * J : nullptr;
+    int j = 0;
+    for (; j + 6 <= J; j += 6) {
+      float4 d[6], s[6];
+#pragma unroll
+      for (int u = 0; u < 6; ++u) {
+        d[u] = stream_load(Dc + (size_t)(j + u) * (kUnitF2 / 2));
+        s[u] = stream_load(Sc + (size_t)(j + u) * (kUnitF2 / 2));
+      }
+#pragma unroll
+      for (int u = 0; u < 6; ++u) acc_unit(a, wc ? (double)wc[j + u] : 1.0, d[u], s[u]);
+    }
+    for (; j < J; ++j)
+      acc_unit(a, wc ? (double)wc[j] : 1.0, stream_load(Dc + (size_t)j * (kUnitF2 / 2)),
+               stream_load(Sc + (size_t)j * (kUnitF2 / 2)));
+  }
+  return a;
+}
+
+// The filter's clipped ratio H = 1 - eta sum w |S|^2 / |sum w D conj(S)|^2 (below
+// 0.2: 0, above 1: 1) of frequency i of the pair.
+__device__ __forceinline__ float scharmer_ratio(const Acc2& a, int i, float eta) {
+  const double mag = a.nr[i] * a.nr[i] + a.ni[i] * a.ni[i];
+  const double v = mag > 0.0 ? 1.0 - (double)eta * a.q[i] / mag : 0.0;
+  return (float)(v < 0.2 ? 0.0 : (v > 1.0 ? 1.0 : v));
+}
+
 // Order of the patch cuts of `units` = P C J (patch, channel, frame) units:
 // frame by frame (f = c J + j), each frame's patches in order, and a contiguous
 // run of that order to each of the 8 XCDs (block b runs on XCD b % 8).  The
@@ -242,9 +286,10 @@ struct FilterTab {
   FilterSpec f[kMaxK];
 };
 // The filters on O in place.  h [P][K][N][N/2+1]: the clipped ratios of the
-// Loefdahl-Scharmer planes (launch_object_filtered); H: the filters, or null.
-hipError_t launch_filter(const Dims& d, const FilterTab& ft, const float* h, float2* O, float* H,
-                         hipStream_t s);
+// Loefdahl-Scharmer planes (launch_object_filtered), or null, and the filter
+// forms them from la.D, la.weights and S.  H: the filters, or null.
+hipError_t launch_filter(const Dims& d, const ChanTab& ct, const FilterTab& ft, const LossArgs& la,
+                         const float2* S, const float* h, float2* O, float* H, hipStream_t s);
 hipError_t launch_mosaic(const Dims& d, const float* obj, int ny, int nx, int stride, int border,
                          float* out, hipStream_t s);
 

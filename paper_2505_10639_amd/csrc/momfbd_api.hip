@@ -622,19 +622,19 @@ int momfbd_object_filtered(momfbd_plan plan, const float* alpha, const void* D,
     });
   // The object pass leaves the filters' clipped ratios, N (N/2 + 1) floats per
   // object, in the gradient's unused buffer, N^2 / 4 floats per frame: from three
-  // frames per object on they fit.  With fewer, in the output's own planes (N^2
-  // floats each), which the inverse transform overwrites last.
+  // frames per object on they fit.  With fewer the filter forms them itself.
   const Dims& d = plan->d;
   const size_t half = (size_t)d.N * (d.N / 2 + 1);
-  float* h = (size_t)d.C * d.J * d.bandpix() >= d.K * half ? w.gphi : obj;
+  float* h = (size_t)d.C * d.J * d.bandpix() >= d.K * half ? w.gphi : nullptr;
   if (e == hipSuccess)
     e = prof_launch(plan, KK_OBJECT, s, [&] {
-      return launch_object_filtered(plan->d, plan->ct, la, ft, w.S, w.O, h, s);
+      return h ? launch_object_filtered(d, plan->ct, la, ft, w.S, w.O, h, s)
+               : launch_object(d, plan->ct, la, nullptr, w.S, w.O, w.loss_pk, nullptr, s, false);
     });
   // the filter scales O in place; momfbd_profile_repeat refuses its kind
   if (e == hipSuccess)
     e = prof_launch(plan, KK_FILTER, s, [&] {
-      return launch_filter(plan->d, ft, h, w.O, H, s);
+      return launch_filter(d, plan->ct, ft, la, w.S, h, w.O, H, s);
     });
   if (e != hipSuccess) return to_status(e);
   return to_status(

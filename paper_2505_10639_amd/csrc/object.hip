@@ -64,10 +64,8 @@ __global__ __launch_bounds__(256) void k_object(int P, int C, int J, int K, Chan
 }
 
 // Frequency pair f2 of a plane whose object takes the Loefdahl-Scharmer filter:
-// the Wiener object as object_pair gives it, and the filter's clipped ratio
-// H = 1 - eta sum w |S|^2 / |sum w D conj(S)|^2 (below 0.2: 0, above 1: 1) from
-// the same sums, which here read S beyond the object's support too (the filter
-// is defined by the OTFs as they are; O is zero there).
+// the Wiener object as object_pair gives it (zero beyond the object's support),
+// and the filter's ratio from the same sums.
 template <int NN>
 __device__ __forceinline__ void scharmer_pair(int f2, int p, int k, int C, int J, int K,
                                               const ChanTab& ct, const LossArgs& la, float eta,
@@ -76,39 +74,11 @@ __device__ __forceinline__ void scharmer_pair(int f2, int p, int k, int C, int J
   constexpr int HC = NN / 2 + 1;
   constexpr int kUnitF2 = NN * HC;
   const int f = 2 * f2;
-  Acc2 a;
-  for (int i = 0; i < 2; ++i) a.nr[i] = a.ni[i] = a.q[i] = a.e[i] = 0.0;
-  const int c0 = ct.obj_first[k], c1 = ct.obj_first[k + 1];
-  for (int ci = c0; ci < c1; ++ci) {
-    const int c = ct.obj_chans[ci];
-    const size_t at = ((size_t)(p * C + c) * J) * kUnitF2 + f;
-    const float4* Dc = reinterpret_cast<const float4*>(la.D + at);
-    const float4* Sc = reinterpret_cast<const float4*>(S + at);
-    const float* wc = la.weights ? la.weights + c * J : nullptr;
-    int j = 0;
-    for (; j + 6 <= J; j += 6) {
-      float4 d[6], s[6];
-#pragma unroll
-      for (int u = 0; u < 6; ++u) {
-        d[u] = stream_load(Dc + (size_t)(j + u) * (kUnitF2 / 2));
-        s[u] = stream_load(Sc + (size_t)(j + u) * (kUnitF2 / 2));
-      }
-#pragma unroll
-      for (int u = 0; u < 6; ++u) acc_unit(a, wc ? (double)wc[j + u] : 1.0, d[u], s[u]);
-    }
-    for (; j < J; ++j)
-      acc_unit(a, wc ? (double)wc[j] : 1.0, stream_load(Dc + (size_t)j * (kUnitF2 / 2)),
-               stream_load(Sc + (size_t)j * (kUnitF2 / 2)));
-  }
-  float h[2];
+  Acc2 a = scharmer_sums<NN>(f2, p, k, C, J, ct, la.D, la.weights, S);
   for (int i = 0; i < 2; ++i) {
-    const double mag = a.nr[i] * a.nr[i] + a.ni[i] * a.ni[i];
-    const double v = mag > 0.0 ? 1.0 - (double)eta * a.q[i] / mag : 0.0;
-    h[i] = (float)(v < 0.2 ? 0.0 : (v > 1.0 ? 1.0 : v));
+    hk[f + i] = scharmer_ratio(a, i, eta);
     a.q[i] += la.gamma ? (double)la.gamma[(size_t)k * kUnitF2 + f + i] : (double)la.gamma_scalar;
   }
-  hk[f] = h[0];
-  hk[f + 1] = h[1];
   const bool sup = in_support(f / HC, NN, la.supp[k * HC + f % HC]) ||
                    in_support((f + 1) / HC, NN, la.supp[k * HC + (f + 1) % HC]);
   if (!sup) a.nr[0] = a.ni[0] = a.nr[1] = a.ni[1] = 0.0;

@@ -14,7 +14,7 @@
 //            apodization".
 //
 // The object pass leaves the clipped ratio on the half spectrum
-// (object.hip).  The filter works on the full N x N grid in LDS (H is symmetric
+// (object.hip) where the workspace has room for it.  The filter works on the full N x N grid in LDS (H is symmetric
 // under u -> -u, so the half spectrum suffices); the island search is a
 // label propagation from the origin repeated until no label changes (at
 // N = 64 on one 64-bit word per row, in one wave).
@@ -80,8 +80,11 @@ __device__ inline unsigned long long shfl64(unsigned long long v, int lane) {
          static_cast<unsigned>(lo);
 }
 
-template <int NN>
-__global__ __launch_bounds__(256) void k_filter(int K, FilterTab ft,
+// OWN: the Loefdahl-Scharmer ratios are formed here, in a pass of their own over
+// D and S, for calls whose workspace has no room for them (h0).
+template <int NN, bool OWN>
+__global__ __launch_bounds__(256) void k_filter(int C, int J, int K, ChanTab ct, FilterTab ft,
+                                                LossArgs la, const float2* __restrict__ S,
                                                 const float* __restrict__ h0,
                                                 float2* __restrict__ O, float* __restrict__ Hout) {
   constexpr int HC = NN / 2 + 1, UNIT = NN * HC, GRID = NN * NN;
@@ -103,8 +106,15 @@ __global__ __launch_bounds__(256) void k_filter(int K, FilterTab ft,
     }
     return;
   }
-  const float* hk = h0 + ((size_t)p * K + k) * UNIT;
-  for (int i = tid; i < UNIT; i += 256) B[i] = hk[i];
+  if constexpr (OWN) {
+    for (int f2 = tid; f2 < UNIT / 2; f2 += 256) {
+      const Acc2 a = scharmer_sums<NN>(f2, p, k, C, J, ct, la.D, la.weights, S);
+      for (int i = 0; i < 2; ++i) B[2 * f2 + i] = scharmer_ratio(a, i, f.noise_power);
+    }
+  } else {
+    const float* hk = h0 + ((size_t)p * K + k) * UNIT;
+    for (int i = tid; i < UNIT; i += 256) B[i] = hk[i];
+  }
   __syncthreads();
   // the full grid: a frequency right of the half spectrum takes its mirror
   // -u (the conjugate pair has the same |num| and den)
@@ -262,17 +272,27 @@ __global__ __launch_bounds__(256) void k_mosaic(int N, int K, int nx, int ny, in
 
 }  // namespace
 
-hipError_t launch_filter(const Dims& d, const FilterTab& ft, const float* h, float2* O, float* H,
-                         hipStream_t s) {
-  const size_t lds = 2 * (size_t)d.N * d.N * sizeof(float);
-  auto* kernel = d.N == 64 ? &k_filter<64> : d.N == 96 ? &k_filter<96> : &k_filter<128>;
+template <int NN>
+static hipError_t launch_filter_n(const Dims& d, const ChanTab& ct, const FilterTab& ft,
+                                  const LossArgs& la, const float2* S, const float* h, float2* O,
+                                  float* H, hipStream_t s) {
+  constexpr size_t lds = 2 * (size_t)NN * NN * sizeof(float);
+  auto* kernel = h ? &k_filter<NN, false> : &k_filter<NN, true>;
   if (lds > 65536) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(kernel, dim3(d.P * d.K), dim3(256), lds, s, d.K, ft, h, O, H);
+  hipLaunchKernelGGL(kernel, dim3(d.P * d.K), dim3(256), lds, s, d.C, d.J, d.K, ct, ft, la, S, h, O,
+                     H);
   return hipGetLastError();
+}
+
+hipError_t launch_filter(const Dims& d, const ChanTab& ct, const FilterTab& ft, const LossArgs& la,
+                         const float2* S, const float* h, float2* O, float* H, hipStream_t s) {
+  return d.N == 64   ? launch_filter_n<64>(d, ct, ft, la, S, h, O, H, s)
+         : d.N == 96 ? launch_filter_n<96>(d, ct, ft, la, S, h, O, H, s)
+                     : launch_filter_n<128>(d, ct, ft, la, S, h, O, H, s);
 }
 
 hipError_t launch_mosaic(const Dims& d, const float* obj, int ny, int nx, int stride, int border,

@@ -320,7 +320,8 @@ int momfbd_lbfgs_rounds(momfbd_plan plan, const momfbd_lbfgs_params* params, voi
  *   sigma   [P] float (device): noise standard deviation per patch
  *   apod    [N][N] float (device)
  *   frames  [C][J][P*N][N] float (device): receives the noisy frames
- *   D       [P][C][J][N][N/2+1] complex64 (device): receives the spectra
+ *   D       [P][C][J][N][N/2+1] complex64 (device): receives the spectra; may
+ *           overlap alpha, O, noise and sigma
  * Every patch size and channel count of the plan.  Errors: EINVAL,
  * EWORKSPACE, EDEVICE. */
 int momfbd_synthesize(momfbd_plan plan, const float* alpha, const void* O, const float* noise,

@@ -440,6 +440,7 @@ hipError_t launch_adjoint64(const Dims& d, const ChanTab& ct, const LossArgs& la
 hipError_t launch_prepare64(const Dims& d, const float* frames, int H, int W, int stride,
                             const float* apod, float2* D, hipStream_t s);
 hipError_t launch_objimg64(const Dims& d, const float2* O, float* obj, hipStream_t s);
+// (D null: the frames only)
 hipError_t launch_burst64(const Dims& d, const ChanTab& ct, const float* Ab, const float* phi,
                           const float2* O, const float* noise, const float* sigma,
                           const float* apod, float* field, float2* D, hipStream_t s);

@@ -563,7 +563,9 @@ __global__ __launch_bounds__(64) void k_netin64(int items, int per, int stride,
 // + m) (as k_prepare64).  S and the frame stay on chip (in three launches S
 // crossed HBM twice and the frames came back once: 23 + 54 + 33 us for 3072
 // units, now 47).  Three waves per SIMD hold those units in one round, at the
-// cost of 16 bytes of scratch a lane (55 us with two).
+// cost of 16 bytes of scratch a lane (55 us with two).  Without SPECTRA the frames
+// only, for a D that overlaps what other units still read.
+template <bool SPECTRA>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_burst64(int units, int P, int C, int J, int K, ChanTab ct,
                                                 const float* __restrict__ Ab,
                                                 const float* __restrict__ phi,
@@ -596,7 +598,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
     v[r] += sg * nz[r * N];
     out[r * N] = v[r];
   }
-  apodized_spectrum<0>(v, apod, Th, Taux, lane, D + (size_t)u * kUnitF2);
+  if constexpr (SPECTRA) apodized_spectrum<0>(v, apod, Th, Taux, lane, D + (size_t)u * kUnitF2);
 }
 
 }  // namespace
@@ -605,8 +607,9 @@ hipError_t launch_burst64(const Dims& d, const ChanTab& ct, const float* Ab, con
                           const float2* O, const float* noise, const float* sigma,
                           const float* apod, float* field, float2* D, hipStream_t s) {
   const int units = d.P * d.C * d.J;
-  hipLaunchKernelGGL(k_burst64, dim3(units), dim3(64), 0, s, units, d.P, d.C, d.J, d.K, ct, Ab,
-                     phi, O, noise, sigma, apod, field, D);
+  auto* kernel = D ? &k_burst64<true> : &k_burst64<false>;
+  hipLaunchKernelGGL(kernel, dim3(units), dim3(64), 0, s, units, d.P, d.C, d.J, d.K, ct, Ab, phi, O,
+                     noise, sigma, apod, field, D);
   return hipGetLastError();
 }
 

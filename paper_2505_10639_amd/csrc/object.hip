@@ -268,12 +268,25 @@ hipError_t launch_frames(int N, int items, int per, int stride, const float2* D,
 hipError_t launch_bursts(const Dims& d, const ChanTab& ct, const float* Ab, const float* phi,
                          float2* S, const float2* O, const float* noise, const float* sigma,
                          const float* apod, float* field, float2* D, hipStream_t s) {
-  if (d.N == 64)
-    return launch_burst64(d, ct, Ab, phi, O, noise, sigma, apod, field, D, s);
-  hipError_t e = launch_forward(d, ct, nullptr, Ab, phi, nullptr, S, s);
-  if (e == hipSuccess)
-    e = d.N == 96 ? launch_synth96(d, ct, O, S, noise, sigma, field, s)
+  const size_t units = (size_t)d.P * d.C * d.J, half = (size_t)d.N * (d.N / 2 + 1);
+  auto over_D = [&](const void* p, size_t bytes) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(D);
+    return a < b + units * half * sizeof(float2) && b < a + bytes;
+  };
+  hipError_t e;
+  if (d.N == 64) {
+    // the spectra in a launch of their own where D shares memory with an input
+    // that the frames of other units come from
+    const bool apart = over_D(O, (size_t)d.P * d.K * half * sizeof(float2)) ||
+                       over_D(noise, units * d.N * d.N * sizeof(float)) ||
+                       over_D(sigma, d.P * sizeof(float));
+    e = launch_burst64(d, ct, Ab, phi, O, noise, sigma, apod, field, apart ? nullptr : D, s);
+    if (!apart) return e;
+  } else {
+    e = launch_forward(d, ct, nullptr, Ab, phi, nullptr, S, s);
+    if (e == hipSuccess) e = d.N == 96 ? launch_synth96(d, ct, O, S, noise, sigma, field, s)
                   : launch_synth128(d, ct, O, S, noise, sigma, field, s);
+  }
   return e != hipSuccess ? e : launch_prepare(d, field, d.P * d.N, d.N, d.N, apod, D, s);
 }
 

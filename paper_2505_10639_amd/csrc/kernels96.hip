@@ -220,6 +220,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
                   F.w.S, F.w.O, F.w.gphi);
 }
 
+// A lane loads its own row of the patch.  Whole rows of the frame in every load
+// (as at 64 and 128, where they pay) made the launch slower here: 15 x 15
+// patches of 24 frames 167 us with 72 pixels of a linear order per thread, whose
+// addresses divide by 96, and 93 with a column per lane (but 61 against 56 at 9 x
+// 9 patches of 39 frames), 94 with these.
 __global__ __launch_bounds__(kThreads) void k_prepare96(CutOrder order, int P, int nframes,
                                                         int H, int W, int stride, int nx,
                                                         const float* __restrict__ frames,
@@ -234,18 +239,16 @@ __global__ __launch_bounds__(kThreads) void k_prepare96(CutOrder order, int P, i
   const bool on = lane < LANES;
   const int y0 = (p / nx) * stride, x0 = (p % nx) * stride;
   const float* src = frames + ((size_t)f * H + y0) * W + x0;
-  // pixel t + 128 i of the patch, in order: whole rows of the frame and of the
-  // window in every load
-  constexpr int kPer = N * N / kThreads;
-  static_assert(kPer * kThreads == N * N && N * 97 <= 2 * LDS_MAIN, "image layout");
-  float* Tf = reinterpret_cast<float*>(T);
-  float v[kPer];
+  float se[48], so[48];
   float sum = 0.f;
+  if (on) {
+    const float* row = src + (size_t)lane * W;
 #pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    const int k = lane + kThreads * i, y = k / N, x = k % N;
-    v[i] = src[(size_t)y * W + x];
-    sum += v[i];
+    for (int n = 0; n < 48; ++n) {
+      se[n] = row[2 * n];
+      so[n] = row[2 * n + 1];
+      sum += se[n] + so[n];
+    }
   }
   red[lane] = sum;
   sync();
@@ -254,22 +257,15 @@ __global__ __launch_bounds__(kThreads) void k_prepare96(CutOrder order, int P, i
     sync();
   }
   const float mean = red[0] * (1.0f / (N * N));
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    const int k = lane + kThreads * i, y = k / N, x = k % N;
-    Tf[y * 97 + x] = apod[k] * (v[i] - mean) + mean;
-  }
-  sync();
-  float se[48], so[48];
   if (on) {
+    const float* wr = apod + lane * N;
 #pragma unroll
     for (int n = 0; n < 48; ++n) {
-      se[n] = Tf[lane * 97 + 2 * n];
-      so[n] = Tf[lane * 97 + 2 * n + 1];
+      se[n] = wr[2 * n] * (se[n] - mean) + mean;
+      so[n] = wr[2 * n + 1] * (so[n] - mean) + mean;
     }
+    op2_rows(se, so, T, lane);
   }
-  sync();
-  if (on) op2_rows(se, so, T, lane);
   sync();
   float2 X[48];
   if (on) op2_cols(T, Taux, lane, X);

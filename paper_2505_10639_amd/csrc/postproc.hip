@@ -212,19 +212,51 @@ __device__ inline double taper1(int x, int N, int b) {
   return e < b ? 0.5 * (1.0 - cos(kPi * (e + 0.5) / b)) : 1.0;
 }
 
-// Eight rows of 256 pixels per block, which computes the taper once.  With a
-// stride of half a patch or more a pixel lies in at most two patches per axis
-// (TWO): its column weights stay in registers and the loads of its four patches
-// are issued together, absent ones as copies of present ones that are not added.
-// 961 patches of two objects of 64 x 64 at stride 32 (39 MB): 14.6 us; the
-// taper per 256 pixels and one load at a time took 19.4.
-constexpr int kMosaicRows = 8;
-template <bool TWO>
+// Any stride: a thread per pixel of all the mosaics, which walks the patches
+// that hold it.  Where these are many (small strides) the walk is the time, and
+// only a thread for each pixel keeps enough of them in flight: 15 x 15 patches
+// of 64 x 64 at stride 5 22 us, 128 with eight rows of pixels per block.
 __global__ __launch_bounds__(256) void k_mosaic(int N, int K, int nx, int ny, int stride,
                                                 int border, int Hm, int Wm,
                                                 const float* __restrict__ obj,
                                                 float* __restrict__ out) {
-  // the 1-D taper of the block's patches, once per block (N <= 128)
+  // the taper of one axis, computed once per workgroup
+  __shared__ double tw[128];
+  for (int e = threadIdx.x; e < N; e += 256) tw[e] = taper1(e, N, border);
+  __syncthreads();
+  const long idx = (long)blockIdx.x * 256 + threadIdx.x;
+  if (idx >= (long)K * Hm * Wm) return;
+  const int k = (int)(idx / ((long)Hm * Wm));
+  const int r = (int)(idx % ((long)Hm * Wm));
+  const int y = r / Wm, x = r % Wm;
+  const int ly = y - N + 1, lx = x - N + 1;
+  const int iy0 = ly <= 0 ? 0 : (ly + stride - 1) / stride, iy1 = min(ny - 1, y / stride);
+  const int ix0 = lx <= 0 ? 0 : (lx + stride - 1) / stride, ix1 = min(nx - 1, x / stride);
+  double acc = 0.0, ws = 0.0;
+  for (int iy = iy0; iy <= iy1; ++iy) {
+    const int ey = y - iy * stride;
+    const double wy = tw[ey];
+    for (int ix = ix0; ix <= ix1; ++ix) {
+      const int ex = x - ix * stride;
+      const double w = wy * tw[ex];
+      acc += w * (double)obj[(((size_t)(iy * nx + ix) * K + k) * N + ey) * N + ex];
+      ws += w;
+    }
+  }
+  out[idx] = (float)(acc / ws);
+}
+
+// With a stride of half a patch or more a pixel lies in at most two patches per
+// axis: eight rows of 256 pixels per block, which computes the taper once; a
+// pixel's column weights stay in registers and the loads of its four patches
+// are issued together, absent ones as copies of present ones that are not added.
+// 961 patches of two objects of 64 x 64 at stride 32 (39 MB): 14.6 us; the
+// kernel above takes 19.4.
+constexpr int kMosaicRows = 8;
+__global__ __launch_bounds__(256) void k_mosaic_two(int N, int K, int nx, int ny, int stride,
+                                                    int border, int Hm, int Wm,
+                                                    const float* __restrict__ obj,
+                                                    float* __restrict__ out) {
   __shared__ double tw[128];
   for (int e = threadIdx.x; e < N; e += 256) tw[e] = taper1(e, N, border);
   __syncthreads();
@@ -245,25 +277,14 @@ __global__ __launch_bounds__(256) void k_mosaic(int N, int K, int nx, int ny, in
       return obj + (((size_t)(iy * nx + ix) * K + k) * N + (y - iy * stride)) * N +
              (x - ix * stride);
     };
-    if (TWO) {
-      const double wy0 = tw[y - iy0 * stride], wy1 = tw[y - iy1 * stride];
-      const float v[4] = {*at(iy0, ix0), *at(iy0, ix1), *at(iy1, ix0), *at(iy1, ix1)};
+    const double wy0 = tw[y - iy0 * stride], wy1 = tw[y - iy1 * stride];
+    const float v[4] = {*at(iy0, ix0), *at(iy0, ix1), *at(iy1, ix0), *at(iy1, ix1)};
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if ((e < 2 || iy1 > iy0) && (e % 2 == 0 || ix1 > ix0)) {
-          const double w = (e < 2 ? wy0 : wy1) * (e % 2 == 0 ? wx0 : wx1);
-          acc += w * (double)v[e];
-          ws += w;
-        }
-      }
-    } else {
-      for (int iy = iy0; iy <= iy1; ++iy) {
-        const double wy = tw[y - iy * stride];
-        for (int ix = ix0; ix <= ix1; ++ix) {
-          const double w = wy * tw[x - ix * stride];
-          acc += w * (double)*at(iy, ix);
-          ws += w;
-        }
+    for (int e = 0; e < 4; ++e) {
+      if ((e < 2 || iy1 > iy0) && (e % 2 == 0 || ix1 > ix0)) {
+        const double w = (e < 2 ? wy0 : wy1) * (e % 2 == 0 ? wx0 : wx1);
+        acc += w * (double)v[e];
+        ws += w;
       }
     }
     out[((size_t)k * Hm + y) * Wm + x] = (float)(acc / ws);
@@ -298,10 +319,15 @@ hipError_t launch_filter(const Dims& d, const ChanTab& ct, const FilterTab& ft, 
 hipError_t launch_mosaic(const Dims& d, const float* obj, int ny, int nx, int stride, int border,
                          float* out, hipStream_t s) {
   const int Hm = (ny - 1) * stride + d.N, Wm = (nx - 1) * stride + d.N;
-  const int blocks = d.K * ((Wm + 255) / 256) * ((Hm + kMosaicRows - 1) / kMosaicRows);
-  auto* kernel = 2 * stride >= d.N ? &k_mosaic<true> : &k_mosaic<false>;
-  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, d.N, d.K, nx, ny, stride, border, Hm,
-                     Wm, obj, out);
+  if (2 * stride >= d.N) {
+    const int blocks = d.K * ((Wm + 255) / 256) * ((Hm + kMosaicRows - 1) / kMosaicRows);
+    hipLaunchKernelGGL(k_mosaic_two, dim3(blocks), dim3(256), 0, s, d.N, d.K, nx, ny, stride, border,
+                       Hm, Wm, obj, out);
+    return hipGetLastError();
+  }
+  const long n = (long)d.K * Hm * Wm;
+  hipLaunchKernelGGL(k_mosaic, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, d.N, d.K, nx,
+                     ny, stride, border, Hm, Wm, obj, out);
   return hipGetLastError();
 }
 

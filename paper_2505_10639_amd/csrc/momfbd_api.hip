@@ -263,6 +263,7 @@ int momfbd_plan_create(const momfbd_desc* desc, const float* pupil, const float*
   const size_t BP = (size_t)B * B;
   std::vector<float> hA((size_t)C * BP, 0.f), hT((size_t)C * BP, 0.f);
   std::vector<float> hZ((size_t)C * M * BP, 0.f);
+  std::vector<int> band(BP);   // the pixel of the frame under each pixel of the band
   for (int c = 0; c < C; ++c) {
     pl->ct.chan_obj[c] = desc->channel_object[c];
     const float* A = pupil + (size_t)c * N * N;
@@ -291,7 +292,8 @@ int momfbd_plan_create(const momfbd_desc* desc, const float* pupil, const float*
     for (int n = 0; n < B; ++n)
       for (int qx = 0; qx < B; ++qx) {
         const int y = ((y0 - oy + n) % N + N) % N, x = ((x0 - ox + qx) % N + N) % N;
-        const size_t src = (size_t)y * N + x, dst = (size_t)n * B + qx;
+        const int src = y * N + x, dst = n * B + qx;
+        band[dst] = src;
         hA[(size_t)c * BP + dst] = A[src];
         const double th = diversity ? diversity[(size_t)c * N * N + src] : 0.0;
         hT[(size_t)c * BP + dst] = (float)(th / kTwoPi);
@@ -299,11 +301,7 @@ int momfbd_plan_create(const momfbd_desc* desc, const float* pupil, const float*
     for (int m = 0; m < M; ++m) {
       const float* Z = basis + ((size_t)c * M + m) * N * N;
       float* z = hZ.data() + ((size_t)c * M + m) * BP;
-      for (int n = 0; n < B; ++n)
-        for (int qx = 0; qx < B; ++qx) {
-          const int y = ((y0 - oy + n) % N + N) % N, x = ((x0 - ox + qx) % N + N) % N;
-          z[(size_t)n * B + qx] = (float)((double)Z[(size_t)y * N + x] / kTwoPi);
-        }
+      for (size_t i = 0; i < BP; ++i) z[i] = (float)((double)Z[band[i]] / kTwoPi);
     }
   }
   // Spectral support of each object: a channel's OTF is nonzero only at
@@ -342,9 +340,6 @@ int momfbd_plan_create(const momfbd_desc* desc, const float* pupil, const float*
   pl->Mp = (M + 15) / 16 * 16;
   pl->Mq = (M + 31) / 32 * 32;
   const int Mp = pl->Mp, Mq = pl->Mq;
-  auto zval = [&](int c, int m, size_t px) {
-    return m < M ? hZ[((size_t)c * M + m) * BP + px] : 0.f;
-  };
   // one lane's eight values of an operand run of 3 parts x 64 lanes
   auto put = [](uint4* run, int lane, const Split8& sp) {
     run[lane] = make_uint4(sp.h[0], sp.h[1], sp.h[2], sp.h[3]);
@@ -358,16 +353,21 @@ int momfbd_plan_create(const momfbd_desc* desc, const float* pupil, const float*
     for (size_t p0 = 0; p0 < BP; p0 += 32)
       for (int m0 = 0; m0 < Mp; m0 += 16, run += 192)
         for (int lane = 0; lane < 64; ++lane) {
-          float v[8];
-          for (int e = 0; e < 8; ++e) v[e] = zval(c, m0 + lane % 16, p0 + lane / 16 * 8 + e);
+          const int m = m0 + lane % 16;
+          if (m >= M) continue;   // padding is zero
+          const float* z = &hZ[((size_t)c * M + m) * BP + p0 + lane / 16 * 8];
+          const float v[8] = {z[0], z[1], z[2], z[3], z[4], z[5], z[6], z[7]};
           put(run, lane, split8(v));
         }
     run = &hZsT[c * (BP / 16) * nk * 192];
     for (size_t p0 = 0; p0 < BP; p0 += 16)
       for (int m0 = 0; m0 < Mq; m0 += 32, run += 192)
         for (int lane = 0; lane < 64; ++lane) {
+          const int m = m0 + lane / 16 * 8;
+          if (m >= M) continue;
+          const float* z = &hZ[((size_t)c * M + m) * BP + p0 + lane % 16];
           float v[8];
-          for (int e = 0; e < 8; ++e) v[e] = zval(c, m0 + lane / 16 * 8 + e, p0 + lane % 16);
+          for (int e = 0; e < 8; ++e) v[e] = m + e < M ? z[e * BP] : 0.f;
           put(run, lane, split8(v));
         }
   }

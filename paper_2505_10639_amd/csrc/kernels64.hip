@@ -408,21 +408,25 @@ __device__ __forceinline__ void apodized_spectrum(float (&v)[64], const float* _
   out[sl_index32(lane)] = x32;
 }
 
-// A workgroup of kPrepWaves units, one per wave: the window is loaded into LDS
+// A workgroup of WAVES units, one per wave.  Four: the window is loaded into LDS
 // once for all of them, beside the loads of the frames.  The 23 064 units of 24
 // frames of 1024 x 1024 take 138 us (490 MB to move, 94 us at the rate of a
-// large copy; 202 us with the window read row by row): the rest is LDS, whose
-// two transposes and the window keep it as busy as the arithmetic.
-constexpr int kPrepWaves = 4;
-__global__ __launch_bounds__(64 * kPrepWaves) void k_prepare64(CutOrder order, int P, int frames_n,
-                                                               int H, int W, int stride, int nx,
-                                                               const float* __restrict__ frames,
-                                                               const float* __restrict__ apod,
-                                                               float2* __restrict__ D) {
-  __shared__ float2 lds[kPrepWaves][LDS_HALF / 2 + LDS_AUX];
-  __shared__ float win[N * N];
+// large copy; 144 with one unit to a workgroup, which reads the window from
+// memory, and 202 us with the window read row by row): the rest is LDS, whose
+// two transposes and the window keep it as busy as the arithmetic.  One, up to
+// kPrepFewUnits units: a chip that they do not fill waits for the window's way
+// through LDS (200 units 8.3 against 9.4 us, 512 8.6 against 10.0, 2880 17.7
+// against 18.0; no difference up to 11 532).
+constexpr int kPrepWaves = 4, kPrepFewUnits = 4096;
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_prepare64(CutOrder order, int P, int frames_n,
+                                                          int H, int W, int stride, int nx,
+                                                          const float* __restrict__ frames,
+                                                          const float* __restrict__ apod,
+                                                          float2* __restrict__ D) {
+  __shared__ float2 lds[WAVES][LDS_HALF / 2 + LDS_AUX];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int g = order.block(blockIdx.x) * kPrepWaves + wave, p = g % P, f = g / P;
+  const int g = order.block(blockIdx.x) * WAVES + wave, p = g % P, f = g / P;
   const bool on = f < frames_n;
   float v[64];
   if (on) {
@@ -431,13 +435,19 @@ __global__ __launch_bounds__(64 * kPrepWaves) void k_prepare64(CutOrder order, i
 #pragma unroll
     for (int r = 0; r < N; ++r) v[r] = src[(size_t)r * W + lane];
   }
+  float2* out = D + ((size_t)p * frames_n + f) * kUnitF2;
+  if constexpr (WAVES > 1) {
+    __shared__ float win[N * N];
 #pragma unroll
-  for (int i = 0; i < N * N / (64 * kPrepWaves); ++i)
-    win[threadIdx.x + 64 * kPrepWaves * i] = apod[threadIdx.x + 64 * kPrepWaves * i];
-  __syncthreads();
-  if (!on) return;
-  apodized_spectrum<1>(v, win, lds[wave], lds[wave] + LDS_HALF / 2, lane,
-                       D + ((size_t)p * frames_n + f) * kUnitF2);
+    for (int i = 0; i < N * N / (64 * WAVES); ++i)
+      win[threadIdx.x + 64 * WAVES * i] = apod[threadIdx.x + 64 * WAVES * i];
+    __syncthreads();
+    if (!on) return;
+    apodized_spectrum<1>(v, win, lds[wave], lds[wave] + LDS_HALF / 2, lane, out);
+  } else {
+    if (!on) return;
+    apodized_spectrum<0>(v, apod, lds[0], lds[0] + LDS_HALF / 2, lane, out);
+  }
 }
 
 // Spectrum in the lanes' layout (X, x32) -> its image IDFT / N^2 in column
@@ -660,9 +670,11 @@ hipError_t launch_prepare64(const Dims& d, const float* frames, int H, int W, in
                             const float* apod, float2* D, hipStream_t s) {
   const int units = d.P * d.C * d.J;
   const int nx = (W - N) / stride + 1;
-  const CutOrder order = CutOrder::of(units, kPrepWaves);
-  hipLaunchKernelGGL(k_prepare64, dim3(order.grid()), dim3(64 * kPrepWaves), 0, s, order, d.P,
-                     d.C * d.J, H, W, stride, nx, frames, apod, D);
+  const int waves = units <= kPrepFewUnits ? 1 : kPrepWaves;
+  const CutOrder order = CutOrder::of(units, waves);
+  auto* kernel = waves == 1 ? &k_prepare64<1> : &k_prepare64<kPrepWaves>;
+  hipLaunchKernelGGL(kernel, dim3(order.grid()), dim3(64 * waves), 0, s, order, d.P, d.C * d.J, H, W,
+                     stride, nx, frames, apod, D);
   return hipGetLastError();
 }
 

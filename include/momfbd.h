@@ -461,14 +461,14 @@ typedef struct {
   int phase_waves;              /* and its waves: 4 x 8 or 8 x 16 (tiles x
                                    waves) while the staged coefficients fit
                                    128 KB of LDS (8 x 16: up to 160 modes).
-                                   0, 0 leaves the shape open: 4 x 8, or 3 x 8
+                                   0, 0 leaves the shape open: 4 x 8, or 2 x 8
                                    for many columns of more than 192 modes, and
                                    up to 128 columns a kernel that stages
-                                   nothing, with the same sums.  get_tuning reports an
-                                   open shape as 8 x 8, from 161 modes on as
-                                   2 x 4, and set_tuning takes it as reported,
-                                   so that a tuning given back restores what
-                                   ran                                        */
+                                   nothing, with the same sums.  get_tuning
+                                   reports an open shape as 8 x 8, from 161
+                                   modes on as 2 x 4, and set_tuning takes it
+                                   as reported, so that a tuning given back
+                                   restores what ran                          */
   int object_fused;             /* 1: the forward transforms and the Wiener
                                    object and loss (Eqs. object_optimization,
                                    loss_momfbd) in one launch, a workgroup per

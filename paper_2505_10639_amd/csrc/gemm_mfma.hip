@@ -200,7 +200,7 @@ hipError_t launch_phase(const Dims& d, const float* alpha, const uint4* ZsT, int
     return hipGetLastError();
   }
   if (shape.ct == 8) return launch_phase_ct<8, 16>(d, alpha, ZsT, Mq, thetat, phi, s);
-  if (shape.ct == 3) return launch_phase_ct<3, 8>(d, alpha, ZsT, Mq, thetat, phi, s);
+  if (shape.ct == 2) return launch_phase_ct<2, 8>(d, alpha, ZsT, Mq, thetat, phi, s);
   return launch_phase_ct<4, 8>(d, alpha, ZsT, Mq, thetat, phi, s);
 }
 

@@ -70,10 +70,12 @@ inline int grad_splits_of(const Dims& d) {
 // 26.7 against 29.5 at 11 532 x 66 (64 x 64), 97 against 129 at 3072 x 150 (128 x
 // 128, four bases); they fit for every mode count.  From 193 modes on they take
 // more than half of a CU's LDS, and a launch of many blocks does better with
-// two blocks of 48 columns there: 200 modes of 64 x 64, 3072 columns 19.2 against
-// 28.6 us (two bases 25.5 against 37.0), 11 532 columns 49 against 61; 1536 columns
-// of 128 x 128, two bases, 47 against 60; but 1000 columns of 64 x 64, two bases,
-// 17.5 against 14.3, and 800 of 96 x 96, one basis, 22.3 against 17.7.
+// three blocks of 32 columns there: 200 modes of 64 x 64, 3072 columns 22.0
+// against 28.8 us (two bases 28.6 against 37.8), 3844 columns 20.3 against 26.5, 11
+// 532 columns 54 against 62; two bases of 96 x 96, 4000 columns, 62 against 66, of
+// 128 x 128, 1536 columns, 51 against 58 (48 columns, two blocks: 19.8, 27.3, 25.0,
+// 52, 64 and 46, but 40 against 35 at 4000 columns of 96 x 96, one basis).  At
+// 800 columns of 96 x 96, one basis, 19.4 against 17.7: fewer blocks keep 64.
 // Up to kFewCols columns the kernel that stages nothing: 3.1 against 5.1 us at 8
 // columns x 44 modes, 4.3 against 12.3 at 128 x 66 (64 x 64), 9 against 16.2 at 120
 // x 150 (128 x 128), but 12.8 against 7.9 at 200 x 66 (96 x 96, three bases).
@@ -88,7 +90,7 @@ inline PhaseShape phase_shape_of(const Dims& d, int Mq) {
   if (R <= kFewCols) return PhaseShape{true, 0, 0};
   const bool one_per_cu = 2 * contract::phase_lds_bytes(4, Mq) > kLdsPerCu;
   const long blocks = 4 * zc * ((R + 63) / 64);   // a quarter of the band each
-  return PhaseShape{false, one_per_cu && blocks >= 3 * kCus / 4 ? 3 : 4, 8};
+  return PhaseShape{false, one_per_cu && blocks >= 3 * kCus / 4 ? 2 : 4, 8};
 }
 
 // A shape that can be selected for Mq padded modes: its staged coefficients

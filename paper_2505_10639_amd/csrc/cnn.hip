@@ -46,9 +46,12 @@ __global__ __launch_bounds__(256) void k_cast_bf16(long n, const float* __restri
 
 // frames [B*J][npix] FP32 -> the network's input, one bfloat16 plane per
 // frame: 10 (f / mean - 1); one block per frame (k_netin64 does the same from
-// the spectra at 64 x 64)
-__global__ __launch_bounds__(256) void k_norm_frames(int npix, const float* __restrict__ f,
-                                                     uint16_t* __restrict__ x) {
+// the spectra at 64 x 64).  WIDE: those values as momfbd_cnn_input returns them,
+// [B][npix][J] floats.
+template <bool WIDE>
+__global__ __launch_bounds__(256) void k_norm_frames(int npix, int J, const float* __restrict__ f,
+                                                     uint16_t* __restrict__ x,
+                                                     float* __restrict__ wide) {
   __shared__ float red[256];
   const int u = blockIdx.x, tid = threadIdx.x;
   const float* fu = f + (long)u * npix;
@@ -61,7 +64,13 @@ __global__ __launch_bounds__(256) void k_norm_frames(int npix, const float* __re
     __syncthreads();
   }
   const float inv = (float)npix / red[0];
-  for (int i = tid; i < npix; i += 256) x[(long)u * npix + i] = f2bf(10.f * (fu[i] * inv - 1.f));
+  for (int i = tid; i < npix; i += 256) {
+    const uint16_t h = f2bf(10.f * (fu[i] * inv - 1.f));
+    if (WIDE)
+      wide[((long)(u / J) * npix + i) * J + u % J] = bf2f(h);
+    else
+      x[(long)u * npix + i] = h;
+  }
 }
 
 // the network's input as momfbd_cnn_input returns it: [B][npix][J] floats
@@ -230,16 +239,23 @@ int split_chunk(const momfbd_cnn_s* n, int M, int N, int K) {
 // W(x - m) + m = IDFT(D) / N^2 of D [B][C][J][N][N/2+1], channel 0, each
 // normalised, one bfloat16 plane per frame
 hipError_t input_from_spectra(const momfbd_cnn_s* n, int B, int C, const void* D, char* ws,
-                              hipStream_t s) {
+                              hipStream_t s, float* wide = nullptr) {
   const float2* d = static_cast<const float2*>(D);
   uint16_t* x0 = reinterpret_cast<uint16_t*>(ws + n->o_x0);
   if (n->N == 64) return launch_netin64(B * n->J, n->J, C * n->J, d, x0, s);
   float* frames = reinterpret_cast<float*>(ws + n->o_frames);
   const hipError_t e = launch_frames(n->N, B * n->J, n->J, C * n->J, d, frames, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_norm_frames, dim3(B * n->J), dim3(256), 0, s, n->N * n->N, frames, x0);
+  auto* kernel = wide ? &k_norm_frames<true> : &k_norm_frames<false>;
+  hipLaunchKernelGGL(kernel, dim3(B * n->J), dim3(256), 0, s, n->N * n->N, n->J, frames, x0, wide);
   return hipGetLastError();
 }
+
+// Frames up to which momfbd_cnn_input writes its floats from the normalisation
+// itself at 96 x 96 and 128 x 128; with more, stores J floats apart cost more than
+// the launch that gathers whole pixels (128 x 128, 64 bursts: 2 frames 40 us
+// against 45, 5 frames 72 against 65, 24 frames 376 against 159).
+constexpr int kDirectInputFrames = 4;
 
 hipError_t run_conv1(const momfbd_cnn_s* n, int B, const uint16_t* x, const uint16_t* w,
                      const float* bias, uint16_t* y, hipStream_t s) {
@@ -565,8 +581,10 @@ int momfbd_cnn_input(momfbd_cnn net, const void* D, int B, int C, float* x, void
   if (!D || !x || C < 1) return MOMFBD_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   char* w = static_cast<char*>(ws);
-  const hipError_t e = input_from_spectra(net, B, C, D, w, s);
+  const bool direct = net->N != 64 && net->J <= kDirectInputFrames;
+  const hipError_t e = input_from_spectra(net, B, C, D, w, s, direct ? x : nullptr);
   if (e != hipSuccess) return MOMFBD_EDEVICE;
+  if (direct) return MOMFBD_OK;
   const int npix = net->N * net->N;
   const long n = (long)B * npix * net->J;
   hipLaunchKernelGGL(k_widen_input, dim3(blocks(n)), dim3(256), 0, s, n, net->J, npix,

@@ -716,4 +716,13 @@ int emu_schedule(const int* dims, const int* set, int* got, int* runs) {
   return 1;
 }
 
+// Patch cuts: the blocks of a launch over `units` units, `per_block` to a block,
+// and each block's place in the frames' order (at most `cap`).
+int emu_cut_order(int units, int per_block, int* out, int cap) {
+  const mfbd::CutOrder order = mfbd::CutOrder::of(units, per_block);
+  const int blocks = (int)order.grid();
+  for (int b = 0; b < blocks && b < cap; ++b) out[b] = order.block(b);
+  return blocks;
+}
+
 }  // extern "C"

@@ -265,7 +265,7 @@ struct CutOrder {
     return CutOrder{((units + per_block - 1) / per_block + 7) / 8};
   }
   __host__ unsigned grid() const { return 8u * (unsigned)per; }
-  __device__ __forceinline__ int block(int b) const { return b % 8 * per + b / 8; }
+  __host__ __device__ __forceinline__ int block(int b) const { return b % 8 * per + b / 8; }
 };
 
 // Smoothness prior constants per object.

@@ -379,7 +379,8 @@ int momfbd_cnn_init(momfbd_cnn net, const float* normals, float* params, void* w
 int momfbd_cnn_load(momfbd_cnn net, const float* params, void* ws, size_t ws_bytes,
                     void* stream);
 /* alpha [B][J][M] float (device) predicted from D [B][C][J][N][N/2+1]
- * (channel 0 is read); B <= batch_max */
+ * (channel 0 is read); B <= batch_max.  A burst's last bits may depend on B
+ * and batch_max, which set the order of a layer's sums. */
 int momfbd_cnn_forward(momfbd_cnn net, const float* params, const void* D, int B, int C,
                        float* alpha, void* ws, size_t ws_bytes, void* stream);
 /* The network's input for D (as momfbd_cnn_forward): x [B][N][N][J] float

@@ -214,7 +214,7 @@ struct momfbd_cnn_s {
   size_t ws_bytes = 0;
   // workspace offsets (bytes)
   size_t o_frames, o_x0, o_y[5], o_z, o_part, o_dz, o_dz2, o_w16, o_lossb;
-  size_t part_floats;   // enters split_chunk: bounds the partial products of a layer's splits
+  size_t part_floats;   // enters split_chunk
   int device = -1;
 };
 
@@ -224,8 +224,10 @@ size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Chunk of the k range summed as one chain (a multiple of 32): as many splits
 // of K as keep 64 x 64 tiles of the output near 2048 blocks and their partial
-// products within part_floats.  It fixes the order of every sum of a layer,
-// whichever kernel forms it.
+// products within part_floats (no such buffer exists: the rule is kept for the
+// bits).  It fixes the order of every sum of a layer, whichever kernel forms it;
+// M is the batch times the layer's rows and part_floats grows with batch_max, so
+// the order, and with it an output's last bits, may change with either.
 int split_chunk(const momfbd_cnn_s* n, int M, int N, int K) {
   const int tm = (M + 63) / 64, tn = (N + 63) / 64;
   const int kc32 = (K + 31) / 32;

@@ -9,10 +9,12 @@
 // one 8-byte store.
 //
 // Order of the sums that are rounded to bfloat16 (activations and their
-// gradients; the network is sensitive to those roundings): the k range of an output is cut into chunks of `kchunk`
-// (a multiple of 32, fixed by the layer's sizes: split_chunk in cnn.hip); a
-// chunk is one chain of matrix instructions in k order from zero, and the
-// chunks are added in order.  Whatever the tiling, an output has the same bits.
+// gradients; the network is sensitive to those roundings): the k range of an
+// output is cut into chunks of `kchunk` (a multiple of 32; split_chunk in
+// cnn.hip); a chunk is one chain of matrix instructions in k order from zero,
+// and the chunks are added in order.  Whatever the tiling, an output has the
+// same bits; but kchunk depends on the rows of the launch, so a burst's bits may
+// differ between batches of different sizes.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -194,7 +196,8 @@ __global__ __launch_bounds__(256) void k_conv(int M, int H, int kchunk,
 // and, at the top, a zero row), the weights beside them, and every wave takes
 // tiles of 16 pixels x 32 channels.  J % 4 == 0: the four k of a lane group
 // are four frames of one tap, one 8-byte read; otherwise four 2-byte reads
-// through a table of offsets.  Read once from memory: 128 B a row and frame.
+// through a table of offsets.  A block reads 2 RO + 1 rows of 2 N bytes a frame,
+// the first of which the block above it reads too.
 __host__ __device__ inline int net_rows(int N) { return N == 64 ? 4 : 2; }
 __host__ __device__ inline int conv1_ld(int J) { return (9 * J + 31) / 32 * 32 + 4; }
 __host__ __device__ inline size_t conv1_tile(int N, int J) {

@@ -263,7 +263,10 @@ MFBD_HDI void op3_cols_fft(float2 (&X)[32], const float2* Taux, int lane) {
     static_for<1, 32>([&](auto I) {
       constexpr int r = decltype(I)::value;
       // fixed roundings: the warm-start network rounds these images to
-      // bfloat16, so they must not depend on the kernel around this operator
+      // bfloat16, so they must not depend on the kernel around this operator.
+      // Which product is fused at which r is no rule of its own: these are the
+      // choices the compiler made in the kernel that first formed the images,
+      // kept so that their bits stay what they were
       X[r] = twmul_fixed<+1, 64, r, r == 8 ? 2 : r % 2 == 0 && r < 16>(X[r]);
     });
   }

@@ -70,9 +70,10 @@ __device__ __forceinline__ Frag2 get_frag(const uint16_t* row, int g) {
 // flight while the current one is multiplied; one barrier a stage.
 // What bounds it: at 256 bursts of 12 frames of 64 x 64 the three layers are
 // 6 GFLOP and move 45 MB, so a launch (10.3 to 11.7 us each) is mostly its
-// start and the latency of its 9 to 18 stages; BM and BN are the smallest
-// tiles that lost nothing, to give every CU blocks at small batches too.  With
-// im2col and partial products in memory the same layers took 55 to 100 us.
+// start and the latency of its 9 to 18 stages (VALU busy 16 to 21% of it); BM
+// and BN are the smallest tiles that lost nothing, to give every CU blocks at
+// small batches too.  With im2col and partial products in memory the same layers
+// took 55 to 100 us.
 template <int CI, int CO, int BM, int BN, int WM, int BK>
 __global__ __launch_bounds__(256) void k_conv(int M, int H, int kchunk,
                                               const uint16_t* __restrict__ x,
@@ -640,9 +641,11 @@ __global__ __launch_bounds__(256) void k_dense_dx(int M, int N, int K, int kchun
 // matrix operands' eight consecutive k are one 16-byte read.  A block is a 64
 // x 64 tile, wave (a, b) 32 x 32 of it, in stages of 32 rows, two of
 // them in flight.  At 256 bursts of 64 x 64 the three convolutions take 20, 19
-// and 14 us with four blocks a CU, most of it the instructions that gather and
-// pair the rows (24, 23 and 15 with two; then, blocks of one row range kept on
-// one XCD: 21, 22, 14, and the dense layers, of few row ranges, 15 instead of 7).
+// and 14 us with four blocks a CU (24, 23 and 15 with two; then, blocks of one
+// row range kept on one XCD: 21, 22, 14, and the dense layers, of few row ranges,
+// 15 instead of 7).  Gathering and pairing the rows takes 26 to 34 VALU
+// instructions to a matrix instruction, yet the VALU is busy only 26 to 32% of
+// the time: the rest is the latency of the stages.
 template <int CI>
 __global__ __launch_bounds__(256) void k_wgrad(int M, int N, int K, int rows, int H,
                                                const uint16_t* __restrict__ P,

@@ -63,23 +63,23 @@ KERNEL_SOURCES = {
     ("forward", 128): ["kernels128.hip", "ops128.h", "fft_lane.h", "internal.h"],
     ("object", 128): ["object.hip", "internal.h"],
 }
-COPY_FETCH_SCALE = 1.9997991127905397   # 256 MiB copy: FETCH_SIZE read 131085.2 KiB
+COPY_FETCH_SCALE = 1.9997991127905397   # 256 MiB copy: FETCH_SIZE read 131085.1 KiB
 COPY_WRITE_SCALE = 1.0    # 256 MiB copy: WRITE_SIZE read 262144 KiB
 # per (kernel, N): the knob and, per value of it, (HBM bytes read, written)
 # per launch
 COUNTED_TRAFFIC = {
-    ("adjoint", 64): {"sources_sha1": "43e02b04e409", "knob": "xcd_adjoint",
-                      "by_value": {1: (895293625, 94470144), 0: (1094380951, 94470144)}},
-    ("forward", 64): {"sources_sha1": "43e02b04e409", "knob": "xcd_forward",
-                      "by_value": {0: (94897868, 404440603), 1: (94900213, 400628168)}},
-    ("object", 64): {"sources_sha1": "cbdbf0cecf85", "knob": "object_pairs_per_thread",
-                     "by_value": {1: (729207388, 32782486)}},
-    ("adjoint", 128): {"sources_sha1": "ad534c1db6d2", "knob": "xcd_adjoint",
-                       "by_value": {1: (11986496049, 1511522304), 0: (13313096194, 1511522304)}},
-    ("forward", 128): {"sources_sha1": "ad534c1db6d2", "knob": "xcd_forward",
-                       "by_value": {0: (3216615743, 8840820484), 1: (3231762912, 8750073519)}},
-    ("object", 128): {"sources_sha1": "cbdbf0cecf85", "knob": "object_pairs_per_thread",
-                      "by_value": {1: (10901719763, 257960210)}},
+    ("adjoint", 64): {"sources_sha1": "2e1fd10d4767", "knob": "xcd_adjoint",
+                      "by_value": {1: (895324235, 94470144), 0: (1094349139, 94470144)}},
+    ("forward", 64): {"sources_sha1": "2e1fd10d4767", "knob": "xcd_forward",
+                      "by_value": {0: (94923515, 404380508), 1: (94920088, 400556004)}},
+    ("object", 64): {"sources_sha1": "c71d64191318", "knob": "object_pairs_per_thread",
+                     "by_value": {1: (729207380, 32782514)}},
+    ("adjoint", 128): {"sources_sha1": "65a629722a1b", "knob": "xcd_adjoint",
+                       "by_value": {1: (11990387525, 1511522304), 0: (13318697413, 1511522304)}},
+    ("forward", 128): {"sources_sha1": "65a629722a1b", "knob": "xcd_forward",
+                       "by_value": {0: (3216004610, 8840373953), 1: (3230101212, 8748303668)}},
+    ("object", 128): {"sources_sha1": "c71d64191318", "knob": "object_pairs_per_thread",
+                      "by_value": {1: (10901719725, 257960147)}},
 }
 
 
